@@ -103,8 +103,12 @@ enum { CDBM_STEP_AUTO = 0, CDBM_STEP_FUSED = 1, CDBM_STEP_SPLIT = 2, CDBM_STEP_F
  *               CDBM_STEP_SPLIT: two single-stage launches, one cell per
  *               thread, f^(1) through a handle-owned buffer (faster on small
  *               grids, where the fused launch has too few strips to fill the
- *               chip).  CDBM_STEP_AUTO: split up to 2^19 cells (724 x 724)
- *               in the mixed form and 2^18 (512 x 512) in FP64, fused
+ *               chip).  CDBM_STEP_AUTO: FP64 and mixed grids of one row run
+ *               several steps per launch, and grids of up to 256 tiles of
+ *               8 x 8 cells one step per launch (both with four lanes per
+ *               cell and both stages in LDS); above that split up to 2^19
+ *               cells (724 x 724) in the mixed form and 2^18 (512 x 512) in
+ *               FP64, fused
  *               above.  CDBM_STEP_FUSED2 (CDBM_MIXED only): two time steps
  *               per launch (temporal blocking: f crosses HBM once in and
  *               once out per two steps, on 48-column strips that carry four
@@ -235,7 +239,8 @@ int cdbm_step_adjoint(cdbm_handle* h, const void* f_n, const void* lam_np1, void
  * Runge-Kutta stage (Sec. 2: the second-order Runge-Kutta scheme in time;
  * with Eq. (1) and the NND derivative of Eqs. (12)-(20) as L):
  * f1_out = f_in + dt L(f_in) and f_out = f_in / 2 + (f1_out + dt L(f1_out)) / 2,
- * as two single-stage launches whatever the handle's step form.  f_in, f1_out,
+ * whatever the handle's step form (one launch where CDBM_STEP_AUTO runs a
+ * step in one tile launch, else two single-stage launches).  f_in, f1_out,
  * f_out: device [16][ny][nx] in the handle's precision, pairwise
  * non-overlapping.  f_out equals what cdbm_step gives for one step bit for
  * bit.  Meant for reverse passes that keep the stages of recomputed steps

@@ -26,6 +26,7 @@ SOURCES = [
     "api_static.hip",
     "kernels_basic.hip",
     "kernels_step.hip",
+    "kernels_quad.hip",
     "kernels_adjoint.hip",
     "kernels_batch.hip",
 ]
@@ -36,6 +37,12 @@ FLAGS = [
     # packed FP32 (v_pk_*_f32) instructions stay off for all device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
+
+# further flags of one source: kernels of a few microseconds get their
+# arguments in registers instead of waiting for a load from a cold cache
+EXTRA = {
+    "kernels_quad.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
+}
 
 
 def hipcc() -> str:
@@ -50,7 +57,7 @@ def _compile(src: str) -> str:
     cmd = [hipcc()]
     if src.endswith(".hip"):
         cmd += ["-x", "hip", f"--offload-arch={ARCH}"]
-    cmd += FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
+    cmd += FLAGS + EXTRA.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"compiling {src} failed:\n{' '.join(cmd)}\n{res.stdout}\n{res.stderr}")

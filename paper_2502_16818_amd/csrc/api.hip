@@ -2,6 +2,7 @@
 // checks, buffer ping-pong, graph capture of the step loop.
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -18,7 +19,8 @@ namespace cdbm {
 
 namespace {
 thread_local std::string g_err;
-constexpr int GRAPH_STEPS = 32;   // steps per captured graph (an even number)
+constexpr int GRAPH_STEPS = 32;   // step launches per captured graph (an even number)
+constexpr int GRAPH_LINE = 8;     // the same for launches of several steps each
 }  // namespace
 
 int fail(int code, const std::string& msg) {
@@ -91,9 +93,9 @@ void StepGraph::release() {
 
 namespace {
 
-// The graph entry that replays GRAPH_STEPS steps into `fout`, captured on
+// The graph entry that replays `len` steps into `fout`, captured on
 // first use.
-int graph_for(StepFn fn, const void* ctx, void* fout, void* scratch, StepGraph& graph,
+int graph_for(StepFn fn, const void* ctx, void* fout, void* scratch, StepGraph& graph, int len,
               StepGraph::Entry** out) {
     for (StepGraph::Entry& en : graph.slot)
         if (en.exec && en.out == fout) {
@@ -122,7 +124,7 @@ int graph_for(StepFn fn, const void* ctx, void* fout, void* scratch, StepGraph& 
     e = hipStreamBeginCapture(graph.cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
     hipError_t le = hipSuccess;
-    for (int s = 0; s < GRAPH_STEPS && le == hipSuccess; ++s)
+    for (int s = 0; s < len && le == hipSuccess; ++s)
         le = (s % 2 == 0) ? fn(ctx, fout, scratch, graph.cap) : fn(ctx, scratch, fout, graph.cap);
     e = hipStreamEndCapture(graph.cap, &g);
     if (le != hipSuccess || e != hipSuccess) {
@@ -143,7 +145,8 @@ int graph_for(StepFn fn, const void* ctx, void* fout, void* scratch, StepGraph& 
 }  // namespace
 
 int run_steps(StepFn fn, const void* ctx, const void* fin, void* fout, void* scratch, int nsteps,
-              hipStream_t st, StepGraph& graph) {
+              hipStream_t st, StepGraph& graph, int graph_len) {
+    if (graph_len <= 0) graph_len = GRAPH_STEPS;
     int remaining = nsteps;
     hipError_t e;
     if (nsteps % 2 == 1) {
@@ -160,15 +163,15 @@ int run_steps(StepFn fn, const void* ctx, const void* fin, void* fout, void* scr
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     const bool can_graph =
         st == nullptr || (hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone);
-    if (can_graph && remaining >= GRAPH_STEPS) {
+    if (can_graph && remaining >= graph_len) {
         StepGraph::Entry* en = nullptr;
-        int rc = graph_for(fn, ctx, fout, scratch, graph, &en);
+        int rc = graph_for(fn, ctx, fout, scratch, graph, graph_len, &en);
         if (rc != CDBM_OK) return rc;
-        while (remaining >= GRAPH_STEPS) {
+        while (remaining >= graph_len) {
             e = hipGraphLaunch(en->exec, st);
             if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
             en->launched = true;
-            remaining -= GRAPH_STEPS;
+            remaining -= graph_len;
         }
         e = hipEventRecord(en->done, st);
         if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
@@ -193,6 +196,9 @@ constexpr int64_t SPLIT_STEP_CELLS_MIXED = int64_t(1) << 19;   // 724 x 724
 constexpr int64_t SPLIT_STEP_CELLS_FP64 = int64_t(1) << 18;    // 512 x 512
 
 hipError_t step_once(const cdbm_handle* h, const void* fin, void* fout, hipStream_t st) {
+    if (h->tile)
+        return mixed(h) ? launch_tile_step<float>(fin, nullptr, fout, h->k, h->qdev, st)
+                        : launch_tile_step<double>(fin, nullptr, fout, h->k, h->qdev, st);
     if (comp(h)) {
         hipError_t e = launch_stage_comp(fin, nullptr, h->stage, false, h->k, h->kdev, st);
         if (e != hipSuccess) return e;
@@ -216,6 +222,13 @@ int check_fields(cdbm_handle* h, const double* rho, const double* ux, const doub
 
 hipError_t step_single(const void* ctx, const void* fin, void* fout, hipStream_t st) {
     return step_once((const cdbm_handle*)ctx, fin, fout, st);
+}
+
+// h->line time steps of a one-row grid in one launch
+hipError_t step_line(const void* ctx, const void* fin, void* fout, hipStream_t st) {
+    const cdbm_handle* h = (const cdbm_handle*)ctx;
+    return mixed(h) ? launch_line_steps<float>(fin, fout, h->line, h->k, h->qdev, st)
+                    : launch_line_steps<double>(fin, fout, h->line, h->k, h->qdev, st);
 }
 
 // two time steps in one launch (CDBM_STEP_FUSED2)
@@ -260,17 +273,29 @@ int cdbm_create(const cdbm_params* p, cdbm_handle** out) {
                (p->step_form == CDBM_STEP_AUTO &&
                 h->cells <= (mixed(h) ? SPLIT_STEP_CELLS_MIXED : SPLIT_STEP_CELLS_FP64));
     h->two = p->step_form == CDBM_STEP_FUSED2;
+    if (p->step_form == CDBM_STEP_AUTO && !comp(h)) {
+        h->line = line_steps_per_launch(h->k);
+        h->tile = h->line == 0 && tile_step_fits(h->k);
+        if (h->line > 0 || h->tile) h->split = false;
+    }
+    struct {
+        QuadParams quad;
+        KParams k;
+    } consts;
+    build_quad(h->k, consts.quad);
+    consts.k = h->k;
     if (ensure_buffer(h, &h->scratch) != CDBM_OK ||
         ((h->split || h->two) && ensure_buffer(h, &h->stage) != CDBM_OK) ||
         hipMalloc(&h->partials, sizeof(double) * 4 * REDUCE_BLOCKS) != hipSuccess ||
         hipMalloc(&h->tau_part, sizeof(double) * tau_blocks) != hipSuccess ||
         hipMalloc(&h->tau_acc, sizeof(double) * stage_adjoint_blocks(h->k)) != hipSuccess ||
         hipMalloc(&h->flag, sizeof(int)) != hipSuccess ||
-        hipMalloc(&h->kdev, sizeof(KParams)) != hipSuccess) {
+        hipMalloc(&h->qdev, sizeof(consts)) != hipSuccess) {
         cdbm_destroy(h);
         return fail(CDBM_ENOMEM, "device allocation failed");
     }
-    e = hipMemcpy(h->kdev, &h->k, sizeof(KParams), hipMemcpyHostToDevice);
+    h->kdev = (KParams*)((char*)h->qdev + offsetof(decltype(consts), k));
+    e = hipMemcpy(h->qdev, &consts, sizeof(consts), hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemset(h->tau_acc, 0, sizeof(double) * stage_adjoint_blocks(h->k));
     if (e != hipSuccess) {
@@ -292,7 +317,7 @@ int cdbm_destroy(cdbm_handle* h) {
     if (h->tau_part) (void)hipFree(h->tau_part);
     if (h->tau_acc) (void)hipFree(h->tau_acc);
     if (h->flag) (void)hipFree(h->flag);
-    if (h->kdev) (void)hipFree(h->kdev);
+    if (h->qdev) (void)hipFree(h->qdev);
     delete h;
     return CDBM_OK;
 }
@@ -344,6 +369,21 @@ int cdbm_step(cdbm_handle* h, const void* f_in, void* f_out, int32_t nsteps, voi
         hipError_t e = launch_step_fused<float>(src, f_out, h->k, h->kdev, st);
         return e == hipSuccess ? CDBM_OK : hip_fail(e, "step launch");
     }
+    if (h->line > 0) {
+        // the steps beyond a multiple of h->line first, in one launch, into
+        // the buffer that the remaining launches do not write next
+        const int units = nsteps / h->line, rest = nsteps % h->line;
+        const void* src = f_in;
+        if (rest > 0) {
+            void* dst = units % 2 == 1 ? h->scratch : f_out;
+            hipError_t e = mixed(h) ? launch_line_steps<float>(f_in, dst, rest, h->k, h->qdev, st)
+                                    : launch_line_steps<double>(f_in, dst, rest, h->k, h->qdev, st);
+            if (e != hipSuccess) return hip_fail(e, "step launch");
+            src = dst;
+        }
+        if (units == 0) return CDBM_OK;
+        return run_steps(step_line, h, src, f_out, h->scratch, units, st, h->graph, GRAPH_LINE);
+    }
     return run_steps(step_single, h, f_in, f_out, h->scratch, nsteps, st, h->graph);
 }
 
@@ -360,6 +400,11 @@ int cdbm_step_keep_stage(cdbm_handle* h, const void* f_in, void* f1_out, void* f
     int rc = check_device(h);
     if (rc != CDBM_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
+    if (h->tile) {
+        hipError_t e = mixed(h) ? launch_tile_step<float>(f_in, f1_out, f_out, h->k, h->qdev, st)
+                                : launch_tile_step<double>(f_in, f1_out, f_out, h->k, h->qdev, st);
+        return e == hipSuccess ? CDBM_OK : hip_fail(e, "step launch");
+    }
     hipError_t e = mixed(h) ? launch_stage<float>(f_in, nullptr, f1_out, false, h->k, h->kdev, st)
                             : launch_stage<double>(f_in, nullptr, f1_out, false, h->k, h->kdev, st);
     if (e == hipSuccess)

@@ -56,11 +56,14 @@ struct cdbm_handle {
     void* stage = nullptr;      // f-sized buffer of a stage-1 state (adjoint, split steps)
     bool split = false;         // step as two single-stage launches (small grids)
     bool two = false;           // two steps per launch (CDBM_STEP_FUSED2)
+    bool tile = false;          // one launch per step, four lanes per cell (small grids)
+    int line = 0;               // steps per launch of a one-row grid (0: not that form)
     void* lam_mid = nullptr;    // f-sized buffer for the adjoint's intermediate product
     double* partials = nullptr; // reduction partials
     double* tau_part = nullptr; // per-block partial sums of the adjoint's tau term (two stages)
     double* tau_acc = nullptr;  // per-block tau terms of step adjoints called without dL_dtau
-    cdbm::KParams* kdev = nullptr;   // device copy of k
+    cdbm::QuadParams* qdev = nullptr;   // device copy of the run constants: for the small-grid
+    cdbm::KParams* kdev = nullptr;      // kernels, and k (one allocation, owned by qdev)
     int* flag = nullptr;        // device flag of the field check
     cdbm::StepGraph graph;
 };
@@ -80,7 +83,8 @@ int check_fields_range(int* flag, const double* rho, const double* ux, const dou
 // Advance nsteps >= 1 from fin to fout (destinations alternate between fout
 // and scratch and end on fout; fin is never written).  Long runs replay a
 // captured graph on `st`, unless `st` is itself being captured (then every
-// step is launched directly into the caller's capture).
+// step is launched directly into the caller's capture).  graph_len: launches
+// per captured graph, even, the same in every call on one `graph` (0: 32).
 int run_steps(StepFn fn, const void* ctx, const void* fin, void* fout, void* scratch,
-              int nsteps, hipStream_t st, StepGraph& graph);
+              int nsteps, hipStream_t st, StepGraph& graph, int graph_len = 0);
 }  // namespace cdbm

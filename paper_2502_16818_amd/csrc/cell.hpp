@@ -74,6 +74,23 @@ struct Macro {
     double rho, ux, uy, T;
 };
 
+// Macroscopic fields of the conserved moments rho, j, 2E; inv_a = 1 / (D + I).
+// Fused operations are written out, here and in nonequilibrium(), so that
+// every kernel rounds the same way whatever else it computes.
+__device__ __forceinline__ Macro macro_of(double rho, double jx, double jy, double e2,
+                                          double inv_a) {
+    // 1 / rho: hardware reciprocal refined by two Newton steps (error ~1 ulp)
+    double inv = __builtin_amdgcn_rcp(rho);
+    inv = fma(inv, fma(-rho, inv, 1.0), inv);
+    inv = fma(inv, fma(-rho, inv, 1.0), inv);
+    Macro m;
+    m.rho = rho;
+    m.ux = jx * inv;
+    m.uy = jy * inv;
+    m.T = fma(e2, inv, -fma(m.ux, m.ux, m.uy * m.uy)) * inv_a;
+    return m;
+}
+
 // `inv_a` = 1 / (D + I).  `z` is a zero offset for the constant-table reads;
 // kernels pass an opaque zero so the compiler reloads the tables where they
 // are used instead of holding them in scalar registers across loops.
@@ -88,16 +105,7 @@ __device__ __forceinline__ Macro macro_from_parity(const Parity& g, const KParam
     }
 #pragma unroll
     for (int c = 0; c < 6; ++c) e2 = fma(K.en[c + z], g.ee[c], e2);
-    // 1 / rho: hardware reciprocal refined by two Newton steps (error ~1 ulp)
-    double inv = __builtin_amdgcn_rcp(rho);
-    inv = fma(inv, fma(-rho, inv, 1.0), inv);
-    inv = fma(inv, fma(-rho, inv, 1.0), inv);
-    Macro m;
-    m.rho = rho;
-    m.ux = jx * inv;
-    m.uy = jy * inv;
-    m.T = (e2 * inv - (m.ux * m.ux + m.uy * m.uy)) * inv_a;
-    return m;
+    return macro_of(rho, jx, jy, e2, inv_a);
 }
 
 // f^eq of the state m (Eq. (7)), through the raw moments and the shared
@@ -160,13 +168,14 @@ __device__ __forceinline__ void equilibrium(const Macro& m, const KParams& K, do
 __device__ __forceinline__ void nonequilibrium(const Parity& g, const Macro& m, const KParams& K,
                                                double a, double out[NV], int z = 0) {
     const double ux = m.ux, uy = m.uy, T = m.T;
-    const double ux2 = ux * ux, uy2 = uy * uy, u2 = ux2 + uy2, uxy = ux * uy;
-    const double aT = a * T;
-    const double A2 = u2 + aT + 2.0 * T;
-    const double A4 = A2 + 2.0 * T;
-    const double mee[6] = {1.0, u2 + aT, ux2 + T, uy2 + T, ux2 * A4 + T * A2, uy2 * A4 + T * A2};
-    const double moe[4] = {ux, ux * A2, ux * (ux2 + 3.0 * T), ux * (uy2 + T)};
-    const double meo[4] = {uy, uy * A2, uy * (ux2 + T), uy * (uy2 + 3.0 * T)};
+    const double ux2 = ux * ux, uy2 = uy * uy, u2 = fma(ux, ux, uy2), uxy = ux * uy;
+    const double E = fma(a, T, u2);        // u^2 + (D+I) T
+    const double A2 = fma(2.0, T, E);
+    const double A4 = fma(2.0, T, A2);
+    const double xx = fma(ux, ux, T), yy = fma(uy, uy, T), TA2 = T * A2;
+    const double mee[6] = {1.0, E, xx, yy, fma(ux2, A4, TA2), fma(uy2, A4, TA2)};
+    const double moe[4] = {ux, ux * A2, ux * fma(3.0, T, ux2), ux * yy};
+    const double meo[4] = {uy, uy * A2, uy * xx, uy * fma(3.0, T, uy2)};
     const double moo[2] = {uxy, uxy * A4};
     const double n2 = -2.0 * m.rho, n4 = -4.0 * m.rho;
     // group of each parity component (k = 2 for a and c, 4 for b and d):

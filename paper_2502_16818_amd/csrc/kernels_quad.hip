@@ -1,0 +1,245 @@
+// Steps of small grids: both Runge-Kutta stages in one launch, four lanes per
+// cell (step_quad.hpp).
+#include <hip/hip_runtime.h>
+
+#include "launch.hpp"
+#include "step_quad.hpp"
+
+namespace cdbm {
+
+namespace {
+
+// The arguments are plain integers and pointers, which reach the wave in
+// registers (the build asks for preloaded arguments); only the constants are
+// behind a pointer.  `bc` holds the boundary kinds, x in bit 0, y in bit 1.
+__device__ __forceinline__ int bc_x(int bc) { return bc & 1; }
+__device__ __forceinline__ int bc_y(int bc) { return bc >> 1; }
+static_assert(CDBM_PERIODIC == 0 && CDBM_ZERO_GRADIENT == 1, "one bit each");
+
+// wrap_or_clamp for an index less than `reach` off the grid: without the
+// division unless the grid is smaller than that.
+__device__ __forceinline__ int wrap_near(int i, int n, int bc, int reach) {
+    if (n < reach) return wrap_or_clamp(i, n, bc);
+    if (bc == CDBM_PERIODIC) return i < 0 ? i + n : (i >= n ? i - n : i);
+    return min(max(i, 0), n - 1);
+}
+
+// One step of a two-dimensional grid.  A block takes an 8 x 8 tile: f^n of
+// the 16 x 16 cells around it goes to LDS, stage 1 runs on the tile and the
+// 2-cell strips beside its four sides (128 cells, one quad each), stage 2 on
+// the tile's 64 cells.  The corners of the halo are not needed: the stencils
+// are crosses.  Bound by latencies: of about 7.6 us from launch to launch at
+// 100 x 100 in FP64, 1.9 until f^n is in LDS, 1.6 stage 1 (two waves per
+// SIMD), 0.8 stage 2, the rest between the launches.  One step of 100 x 100 in
+// FP64 14.7 -> 7.6 us against the two single-stage launches; a call of one
+// step on 32 x 32 (mixed) 11.3 -> 8.4 us.
+constexpr int TILE = 8, TW0 = TILE + 8, TN0 = TW0 * TW0, TW1 = TILE + 4, TN1 = TW1 * TW1;
+constexpr int TILE_THREADS = 4 * (TILE * TILE + 8 * TILE);
+
+template <typename S>
+__global__ void __launch_bounds__(TILE_THREADS) k_tile_step(const S* __restrict__ fin,
+                                                            const QuadParams* __restrict__ Qd,
+                                                            int nx, int ny, int bc,
+                                                            S* __restrict__ fout,
+                                                            S* __restrict__ f1out) {
+    __shared__ __attribute__((aligned(32))) S F0[NV * TN0];
+    __shared__ __attribute__((aligned(32))) S F1[NV * TN1];
+    const int64_t cells = (int64_t)nx * ny;
+    const int x0 = blockIdx.x * TILE, y0 = blockIdx.y * TILE;
+    const int tid = threadIdx.x, q = tid & 3;
+    const QuadLane L = quad_lane(q);
+    QuadConst<S> Q;
+    {
+        const int cell = tid & (TN0 - 1);
+        const int gx = wrap_near(x0 - 4 + (cell & (TW0 - 1)), nx, bc_x(bc), TW0);
+        const int gy = wrap_near(y0 - 4 + cell / TW0, ny, bc_y(bc), TW0);
+        // a thread takes whole groups of its cell, so that each goes to LDS in
+        // one piece; the planes' starts are scalar, the offset within one 32 bits
+        constexpr int GRP = TN0 * 4 / TILE_THREADS;
+        const int g0 = __builtin_amdgcn_readfirstlane(tid / TN0) * GRP;
+        const uint32_t off = (uint32_t)(gy * nx + gx) * (uint32_t)sizeof(S);
+        typename Quad4<S>::type v[GRP];
+#pragma unroll
+        for (int g = 0; g < GRP; ++g)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                v[g][k] = *(const S*)((const char*)(fin + (int64_t)(4 * (g0 + g) + k) * cells) + off);
+        Q = quad_const<S>(Qd, L);
+#pragma unroll
+        for (int g = 0; g < GRP; ++g)
+            *(typename Quad4<S>::type*)(F0 + ((g0 + g) * TN0 + cell) * 4) = v[g];
+    }
+    // the quad's cell: the tile row by row, then the strips left, right, above, below
+    const int t = tid >> 2;
+    int lx, ly;   // in the 16 x 16 cells
+    if (t < TILE * TILE) {
+        lx = 4 + t % TILE;
+        ly = 4 + t / TILE;
+    } else {
+        const int u = t - TILE * TILE, side = u / (2 * TILE), v = u % (2 * TILE);
+        lx = side < 2 ? (side == 0 ? 2 : TILE + 4) + v % 2 : 4 + v % TILE;
+        ly = side < 2 ? 4 + v / 2 : (side == 2 ? 2 : TILE + 4) + v / TILE;
+    }
+    const bool zx = bc_x(bc) == CDBM_ZERO_GRADIENT, zy = bc_y(bc) == CDBM_ZERO_GRADIENT;
+    const int xlo = zx ? max(0, 4 - x0) : 0, xhi = zx ? min(TW0 - 1, nx - 1 - x0 + 4) : TW0 - 1;
+    const int ylo = zy ? max(0, 4 - y0) : 0, yhi = zy ? min(TW0 - 1, ny - 1 - y0 + 4) : TW0 - 1;
+    const int here = ly * TW0 + lx;
+    const QuadStencil st0 = quad_stencil<false>(L, lx, ly, TW0, xlo, xhi, ylo, yhi);
+    __syncthreads();
+    S fc[4], f1[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) fc[g] = F0[(g * TN0 + here) * 4 + q];
+    {
+        quad_stage<S, TN0, false, false>(F0, here, st0, fc, L, Q, f1);
+    }
+    const int here1 = (ly - 2) * TW1 + lx - 2;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) F1[(g * TN1 + here1) * 4 + q] = f1[g];
+    __syncthreads();
+    const int x = x0 + lx - 4, y = y0 + ly - 4;
+    if (t >= TILE * TILE) return;   // whole waves
+    const bool inside = x < nx && y < ny;
+    // byte offset of the cell in the plane of the lane's velocity, from group a's
+    const uint32_t at = ((uint32_t)q * (uint32_t)cells + (uint32_t)(y * nx + x)) * (uint32_t)sizeof(S);
+    if (f1out != nullptr && inside) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *(S*)((char*)(f1out + (int64_t)(4 * g) * cells) + at) = f1[g];
+    }
+    S out[4];
+    {
+        const QuadStencil st =
+            quad_stencil<false>(L, lx - 2, ly - 2, TW1, max(xlo - 2, 0), min(xhi - 2, TW1 - 1),
+                                max(ylo - 2, 0), min(yhi - 2, TW1 - 1));
+        quad_stage<S, TN1, true, false>(F1, here1, st, f1, L, Q, out);
+    }
+    if (inside) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *(S*)((char*)(fout + (int64_t)(4 * g) * cells) + at) = fma(S(0.5), fc[g], out[g]);
+    }
+}
+
+// `steps` steps of a grid of one row (a tube).  A block holds LINE_CELLS
+// consecutive cells in LDS, one quad each; a step makes the outer four on
+// either side stale, and the LINE_CELLS - 8 steps cells in the middle are
+// written.  Bound by the instructions of one wave per SIMD (about 235 a
+// stage, 0.55 us).  Per step, FP64, 500 cells: 10.1 -> 1.8 us against the two
+// single-stage launches; mixed, 10000 cells: 9.4 -> 2.2 us.
+constexpr int LINE_CELLS = 64;
+
+template <typename S>
+__global__ void __launch_bounds__(4 * LINE_CELLS) k_line_steps(const S* __restrict__ fin,
+                                                               const QuadParams* __restrict__ Qd,
+                                                               int nx, int bc, int steps,
+                                                               S* __restrict__ fout) {
+    constexpr int W = LINE_CELLS;
+    __shared__ __attribute__((aligned(32))) S F0[NV * W];
+    __shared__ __attribute__((aligned(32))) S F1[NV * W];
+    const int x0 = blockIdx.x * (W - 8 * steps) - 4 * steps;
+    const int tid = threadIdx.x, q = tid & 3, lx = tid >> 2;
+    const QuadLane L = quad_lane(q);
+    QuadConst<S> Q;
+    {
+        const int cell = tid & (W - 1), g = __builtin_amdgcn_readfirstlane(tid / W);
+        const uint32_t off =
+            (uint32_t)wrap_near(x0 + cell, nx, bc_x(bc), W) * (uint32_t)sizeof(S);
+        typename Quad4<S>::type v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            v[k] = *(const S*)((const char*)(fin + (int64_t)(4 * g + k) * nx) + off);
+        Q = quad_const<S>(Qd, L);
+        *(typename Quad4<S>::type*)(F0 + (g * W + cell) * 4) = v;
+    }
+    const bool zx = bc_x(bc) == CDBM_ZERO_GRADIENT;
+    const int xlo = zx ? min(max(0, -x0), W - 1) : 0;
+    const int xhi = zx ? min(W - 1, nx - 1 - x0) : W - 1;
+    const QuadStencil st = quad_stencil<true>(L, lx, 0, W, xlo, xhi, 0, 0);
+    __syncthreads();
+    S fc[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) fc[g] = F0[(g * W + lx) * 4 + q];
+    for (int s = 0; s < steps; ++s) {
+        S f1[4], out[4];
+        quad_stage<S, W, false, true>(F0, lx, st, fc, L, Q, f1);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) F1[(g * W + lx) * 4 + q] = f1[g];
+        __syncthreads();
+        quad_stage<S, W, true, true>(F1, lx, st, f1, L, Q, out);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) fc[g] = fma(S(0.5), fc[g], out[g]);
+        if (s + 1 < steps) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) F0[(g * W + lx) * 4 + q] = fc[g];
+            __syncthreads();
+        }
+    }
+    const int x = x0 + lx;
+    if (lx >= 4 * steps && lx < W - 4 * steps && x < nx) {
+        const uint32_t at = (uint32_t)(q * nx + x) * (uint32_t)sizeof(S);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) *(S*)((char*)(fout + (int64_t)(4 * g) * nx) + at) = fc[g];
+    }
+}
+
+}  // namespace
+
+// One block per compute unit at most: a block's stages are bound by the
+// latency of two waves per SIMD, and with a second round of blocks the two
+// launches of the single-stage kernels are as fast (mixed / FP64: 128 x 128,
+// 256 blocks, 8 / 11 us against 12 / 15; 160 x 160, 400 blocks, 11 / 17
+// against 12 / 16; 256 x 256 20 / 29 against 15 / 20).
+bool tile_step_fits(const KParams& K) {
+    return (int64_t)((K.nx + TILE - 1) / TILE) * ((K.ny + TILE - 1) / TILE) <= device_cus();
+}
+
+// A launch of k steps costs about 2.4 us and 1.25 us per step and round of
+// one block per compute unit; more steps per launch mean fewer cells written
+// per block, so the best k falls with the length of the row (us per step,
+// FP64, measured for k = 1 / 4 / 7: 500 cells 3.7 / 1.9 / 1.7; 10000 cells
+// 4.0 / 2.9 / 5.4, k = 3 2.4; 65536 cells 10 / 9 / 30).
+int line_steps_per_launch(const KParams& K) {
+    if (K.ny != 1) return 0;
+    const int cus = device_cus();
+    int best = 1;
+    double cost = 0.0;
+    for (int k = 1; 8 * k < LINE_CELLS; ++k) {
+        const int out = LINE_CELLS - 8 * k;
+        const int blocks = (K.nx + out - 1) / out, rounds = (blocks + cus - 1) / cus;
+        const double c = (2.0 + rounds * k) / k;
+        if (k == 1 || c < cost) {
+            cost = c;
+            best = k;
+        }
+    }
+    return best;
+}
+
+template <typename S>
+hipError_t launch_tile_step(const void* fin, void* f1out, void* fout, const KParams& K,
+                            const QuadParams* Qd, hipStream_t st) {
+    const dim3 grid((K.nx + TILE - 1) / TILE, (K.ny + TILE - 1) / TILE);
+    hipLaunchKernelGGL(k_tile_step<S>, grid, dim3(TILE_THREADS), 0, st, (const S*)fin, Qd, K.nx,
+                       K.ny, K.bcx | K.bcy << 1, (S*)fout, (S*)f1out);
+    return hipGetLastError();
+}
+
+template <typename S>
+hipError_t launch_line_steps(const void* fin, void* fout, int steps, const KParams& K,
+                             const QuadParams* Qd, hipStream_t st) {
+    const int out = LINE_CELLS - 8 * steps;
+    hipLaunchKernelGGL(k_line_steps<S>, dim3((K.nx + out - 1) / out), dim3(4 * LINE_CELLS), 0, st,
+                       (const S*)fin, Qd, K.nx, K.bcx, steps, (S*)fout);
+    return hipGetLastError();
+}
+
+#define CDBM_INSTANTIATE(S)                                                                       \
+    template hipError_t launch_tile_step<S>(const void*, void*, void*, const KParams&,           \
+                                            const QuadParams*, hipStream_t);                        \
+    template hipError_t launch_line_steps<S>(const void*, void*, int, const KParams&,            \
+                                             const QuadParams*, hipStream_t);
+CDBM_INSTANTIATE(float)
+CDBM_INSTANTIATE(double)
+#undef CDBM_INSTANTIATE
+
+}  // namespace cdbm

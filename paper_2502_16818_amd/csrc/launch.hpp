@@ -55,6 +55,20 @@ hipError_t launch_step_fused(const void* fin, void* fout, const KParams& K, cons
 hipError_t launch_step2_fused(const void* fin, void* fout, const KParams& K, const KParams* Kd,
                               hipStream_t st);
 
+// Small grids, four lanes per cell (kernels_quad.hip): one step in one launch
+// (f1out: its first stage, or null), and `steps` steps (1 .. 7) of a one-row
+// grid.  tile_step_fits: is the grid small enough for the first to be the
+// fastest form?  line_steps_per_launch: steps per launch for a one-row grid, 0
+// for any other.
+bool tile_step_fits(const KParams& K);
+int line_steps_per_launch(const KParams& K);
+template <typename S>
+hipError_t launch_tile_step(const void* fin, void* f1out, void* fout, const KParams& K,
+                            const QuadParams* Qd, hipStream_t st);
+template <typename S>
+hipError_t launch_line_steps(const void* fin, void* fout, int steps, const KParams& K,
+                             const QuadParams* Qd, hipStream_t st);
+
 // Adjoint (kernels_adjoint.hip).  tau_part: one double per block
 // (stage_adjoint_blocks), the block sums of the launch's tau term, written
 // or (tau_add) added to what it holds.

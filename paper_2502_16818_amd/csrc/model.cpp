@@ -294,4 +294,36 @@ int build_params(const cdbm_params& p, KParams& k, std::string& err) {
     return CDBM_OK;
 }
 
+void build_quad(const KParams& k, QuadParams& r) {
+    std::memset(&r, 0, sizeof(r));
+    for (int p = 0; p < 2; ++p) {
+        // velocities 8p, 8p + 1 and 8p + 4 move towards larger indices
+        for (int c = 0; c < 6; ++c) r.lane.eep[p][c] = k.eep[p][c];
+        for (int c = 0; c < 4; ++c) {
+            r.lane.ox[p][c] = k.ioe[2 * p][c];
+            r.lane.oy[p][c] = k.ieo[2 * p][c];
+        }
+        r.lane.ax[p] = k.cx[8 * p];
+        r.lane.ay[p] = k.cy[8 * p + 1];
+        r.lane.dx[p] = k.cx[8 * p + 4];
+        r.lane.dy[p] = k.cy[8 * p + 4];
+        r.lane.nz[p] = k.nzq[0][p];
+    }
+    for (int p = 0; p < 2; ++p) {
+        for (int c = 0; c < 4; ++c) {
+            r.s.diag[p].ees[c] = k.ees[p][c];
+            r.s.diag[p].ioe[c] = k.ioe[2 * p + 1][c];
+            r.s.diag[p].ieo[c] = k.ieo[2 * p + 1][c];
+        }
+        for (int c = 0; c < 2; ++c) r.s.diag[p].ioo[c] = k.ioo[p][c];
+    }
+    for (int c = 0; c < 4; ++c) r.s.jv[c] = k.jx[c];
+    r.s.en_a = k.en[0];
+    r.s.en_b = k.en[2];
+    r.s.en_c = k.en[3];
+    r.s.en_d = k.en[5];
+    r.s.a = k.a;
+    r.s.inv_a = k.inv_a;
+}
+
 }  // namespace cdbm

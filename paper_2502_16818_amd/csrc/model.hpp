@@ -73,6 +73,34 @@ struct KParams {
     int32_t nx, ny, bcx, bcy;
 };
 
+// The constants of the four-lanes-per-cell kernels (step_quad.hpp).
+struct alignas(64) QuadParams {
+    // From these each lane forms its own: eep as in KParams, the rows of the
+    // axis pairs odd along x (ioe) and along y (ieo), the NND coefficients
+    // -dt v / dr of the first stage of velocities towards larger indices
+    // (groups a, c along x and along y, groups b, d along x and along y) and
+    // the relaxation factors of the first stage (KParams::nzq).
+    struct Lane {
+        double eep[2][6], ox[2][4], oy[2][4];
+        double ax[2], ay[2], dx[2], dy[2], nz[2];
+        double pad[2];
+    } lane;
+    // Those that all lanes use as they are: the rows of the diagonal groups b
+    // and d; the speeds (the rows of the momenta, along x and along y the
+    // same); the row of the energy (KParams::en, equal for an axis pair).
+    struct Shared {
+        struct Diag {
+            double ees[4], ioe[4], ieo[4], ioo[2];
+        } diag[2];
+        double jv[4], en_a, en_b, en_c, en_d, a, inv_a;
+        double pad[2];
+    } s;
+};
+static_assert(sizeof(QuadParams::Lane) == 5 * 64 && sizeof(QuadParams::Shared) == 5 * 64,
+              "quad_const() touches each 64-byte line");
+
+void build_quad(const KParams& k, QuadParams& q);
+
 // Validate p and fill k.  Returns CDBM_OK or an error code with a message.
 int build_params(const cdbm_params& p, KParams& k, std::string& err);
 
