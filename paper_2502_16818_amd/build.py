@@ -26,6 +26,7 @@ SOURCES = [
     "api_static.hip",
     "kernels_basic.hip",
     "kernels_step.hip",
+    "kernels_stage.hip",
     "kernels_quad.hip",
     "kernels_adjoint.hip",
     "kernels_batch.hip",
@@ -42,6 +43,7 @@ FLAGS = [
 # arguments in registers instead of waiting for a load from a cold cache
 EXTRA = {
     "kernels_quad.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
+    "kernels_stage.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
 }
 
 

@@ -200,16 +200,16 @@ hipError_t step_once(const cdbm_handle* h, const void* fin, void* fout, hipStrea
         return mixed(h) ? launch_tile_step<float>(fin, nullptr, fout, h->k, h->qdev, st)
                         : launch_tile_step<double>(fin, nullptr, fout, h->k, h->qdev, st);
     if (comp(h)) {
-        hipError_t e = launch_stage_comp(fin, nullptr, h->stage, false, h->k, h->kdev, st);
+        hipError_t e = launch_stage_comp(fin, nullptr, h->stage, false, h->k, h->sdev, st);
         if (e != hipSuccess) return e;
-        return launch_stage_comp(h->stage, fin, fout, true, h->k, h->kdev, st);
+        return launch_stage_comp(h->stage, fin, fout, true, h->k, h->sdev, st);
     }
     if (h->split) {
-        hipError_t e = mixed(h) ? launch_stage<float>(fin, nullptr, h->stage, false, h->k, h->kdev, st)
-                                : launch_stage<double>(fin, nullptr, h->stage, false, h->k, h->kdev, st);
+        hipError_t e = mixed(h) ? launch_stage<float>(fin, nullptr, h->stage, false, h->k, h->sdev, st)
+                                : launch_stage<double>(fin, nullptr, h->stage, false, h->k, h->sdev, st);
         if (e != hipSuccess) return e;
-        return mixed(h) ? launch_stage<float>(h->stage, fin, fout, true, h->k, h->kdev, st)
-                        : launch_stage<double>(h->stage, fin, fout, true, h->k, h->kdev, st);
+        return mixed(h) ? launch_stage<float>(h->stage, fin, fout, true, h->k, h->sdev, st)
+                        : launch_stage<double>(h->stage, fin, fout, true, h->k, h->sdev, st);
     }
     return mixed(h) ? launch_step_fused<float>(fin, fout, h->k, h->kdev, st)
                     : launch_step_fused<double>(fin, fout, h->k, h->kdev, st);
@@ -280,9 +280,11 @@ int cdbm_create(const cdbm_params* p, cdbm_handle** out) {
     }
     struct {
         QuadParams quad;
+        StageParams stage;
         KParams k;
     } consts;
     build_quad(h->k, consts.quad);
+    build_stage(h->k, consts.stage);
     consts.k = h->k;
     if (ensure_buffer(h, &h->scratch) != CDBM_OK ||
         ((h->split || h->two) && ensure_buffer(h, &h->stage) != CDBM_OK) ||
@@ -294,6 +296,7 @@ int cdbm_create(const cdbm_params* p, cdbm_handle** out) {
         cdbm_destroy(h);
         return fail(CDBM_ENOMEM, "device allocation failed");
     }
+    h->sdev = (StageParams*)((char*)h->qdev + offsetof(decltype(consts), stage));
     h->kdev = (KParams*)((char*)h->qdev + offsetof(decltype(consts), k));
     e = hipMemcpy(h->qdev, &consts, sizeof(consts), hipMemcpyHostToDevice);
     if (e == hipSuccess)
@@ -405,11 +408,11 @@ int cdbm_step_keep_stage(cdbm_handle* h, const void* f_in, void* f1_out, void* f
                                 : launch_tile_step<double>(f_in, f1_out, f_out, h->k, h->qdev, st);
         return e == hipSuccess ? CDBM_OK : hip_fail(e, "step launch");
     }
-    hipError_t e = mixed(h) ? launch_stage<float>(f_in, nullptr, f1_out, false, h->k, h->kdev, st)
-                            : launch_stage<double>(f_in, nullptr, f1_out, false, h->k, h->kdev, st);
+    hipError_t e = mixed(h) ? launch_stage<float>(f_in, nullptr, f1_out, false, h->k, h->sdev, st)
+                            : launch_stage<double>(f_in, nullptr, f1_out, false, h->k, h->sdev, st);
     if (e == hipSuccess)
-        e = mixed(h) ? launch_stage<float>(f1_out, f_in, f_out, true, h->k, h->kdev, st)
-                     : launch_stage<double>(f1_out, f_in, f_out, true, h->k, h->kdev, st);
+        e = mixed(h) ? launch_stage<float>(f1_out, f_in, f_out, true, h->k, h->sdev, st)
+                     : launch_stage<double>(f1_out, f_in, f_out, true, h->k, h->sdev, st);
     return e == hipSuccess ? CDBM_OK : hip_fail(e, "stage launch");
 }
 

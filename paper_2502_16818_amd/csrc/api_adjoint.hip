@@ -31,7 +31,7 @@ int step_adjoint_impl(cdbm_handle* h, const void* f_n, const void* f1, const voi
     const int nb = stage_adjoint_blocks(K);
     hipError_t e = hipSuccess;
     if (!f1) {
-        e = launch_stage<S>(f_n, nullptr, h->stage, false, K, h->kdev, st);
+        e = launch_stage<S>(f_n, nullptr, h->stage, false, K, h->sdev, st);
         if (e != hipSuccess) return hip_fail(e, "stage recompute launch");
         f1 = h->stage;
     }

@@ -62,8 +62,10 @@ struct cdbm_handle {
     double* partials = nullptr; // reduction partials
     double* tau_part = nullptr; // per-block partial sums of the adjoint's tau term (two stages)
     double* tau_acc = nullptr;  // per-block tau terms of step adjoints called without dL_dtau
-    cdbm::QuadParams* qdev = nullptr;   // device copy of the run constants: for the small-grid
-    cdbm::KParams* kdev = nullptr;      // kernels, and k (one allocation, owned by qdev)
+    // device copies of the run constants, in one allocation owned by qdev
+    cdbm::QuadParams* qdev = nullptr;    // small-grid kernels
+    cdbm::StageParams* sdev = nullptr;   // single stages
+    cdbm::KParams* kdev = nullptr;       // k
     int* flag = nullptr;        // device flag of the field check
     cdbm::StepGraph graph;
 };

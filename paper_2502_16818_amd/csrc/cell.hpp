@@ -165,7 +165,9 @@ __device__ __forceinline__ void equilibrium(const Macro& m, const KParams& K, do
 // combinations of f and B m-hat the (row-scaled by 1/k) block contraction,
 // the parity combinations of k (f - f^eq) are g_r - k rho (B m-hat)_r, and
 // unpacking them (additions only) gives k (f_i - f_i^eq).
-__device__ __forceinline__ void nonequilibrium(const Parity& g, const Macro& m, const KParams& K,
+// Table: const KParams or const StageParams (in any address space).
+template <class Table>
+__device__ __forceinline__ void nonequilibrium(const Parity& g, const Macro& m, Table& K,
                                                double a, double out[NV], int z = 0) {
     const double ux = m.ux, uy = m.uy, T = m.T;
     const double ux2 = ux * ux, uy2 = uy * uy, u2 = fma(ux, ux, uy2), uxy = ux * uy;
@@ -205,7 +207,7 @@ __device__ __forceinline__ void nonequilibrium(const Parity& g, const Macro& m, 
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             so = fma(K.ioe[r][c + z], moe[c], so);
-            se = fma(K.ieo[r][c + z], meo[c], se);
+            se = fma(K.ioe[r][(c < 2 ? c : 5 - c) + z], meo[c], se);   // ieo
         }
         const double n = (r & 1) ? n4 : n2;
         toe[r] = fma(n, so, g.oe[r]);

@@ -1,11 +1,10 @@
-// Point-wise and simple stencil kernels of the CDBM library: initial
-// equilibrium, field checks, macroscopic moments, nonequilibrium measures,
-// conserved totals and the unfused Runge-Kutta stage.
+// Point-wise kernels of the CDBM library: initial
+// equilibrium, field checks, macroscopic moments, nonequilibrium measures and
+// conserved totals.
 #include <hip/hip_runtime.h>
 
 #include "cell.hpp"
 #include "launch.hpp"
-#include "step_fused.hpp"
 
 namespace cdbm {
 
@@ -86,27 +85,6 @@ __device__ __forceinline__ void load_residual(const float* __restrict__ f, int64
                                               int64_t c, double r[4]) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) r[k] = (double)f[(NV + k) * cells + c];
-}
-
-// An empty asm statement that takes the values as register operands: every
-// load feeding them completes before it, and none of them is used before
-// it, so the loads are issued together rather than one at a time.
-__device__ __forceinline__ void hold_values(float (&v)[4]) {
-    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
-}
-__device__ __forceinline__ void hold_values(float (&v)[NV + 4]) {
-    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]),
-                 "+v"(v[6]), "+v"(v[7]), "+v"(v[8]), "+v"(v[9]));
-    asm volatile("" : "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]),
-                 "+v"(v[15]), "+v"(v[16]), "+v"(v[17]), "+v"(v[18]), "+v"(v[19]));
-}
-__device__ __forceinline__ void hold_values(float (&v)[4][6]) {
-    asm volatile("" : "+v"(v[0][0]), "+v"(v[0][1]), "+v"(v[0][2]), "+v"(v[0][3]), "+v"(v[0][4]),
-                 "+v"(v[0][5]), "+v"(v[1][0]), "+v"(v[1][1]), "+v"(v[1][2]), "+v"(v[1][3]),
-                 "+v"(v[1][4]), "+v"(v[1][5]));
-    asm volatile("" : "+v"(v[2][0]), "+v"(v[2][1]), "+v"(v[2][2]), "+v"(v[2][3]), "+v"(v[2][4]),
-                 "+v"(v[2][5]), "+v"(v[3][0]), "+v"(v[3][1]), "+v"(v[3][2]), "+v"(v[3][3]),
-                 "+v"(v[3][4]), "+v"(v[3][5]));
 }
 
 // Compensated initial state: f = f^eq rounded to float, r = the conserved
@@ -261,174 +239,6 @@ __global__ void __launch_bounds__(256) k_sum_partials(const double* __restrict__
     }
 }
 
-// Global-memory neighbour access with boundary conditions, for the unfused stage.
-template <typename S>
-struct GlobalLd {
-    const S* __restrict__ f;
-    int64_t cells;
-    int nx;
-    int xs[5];   // source columns of offsets -2..2
-    int ys[5];   // source rows of offsets -2..2
-    __device__ __forceinline__ S operator()(int i, int ox, int oy) const {
-        return f[i * cells + (int64_t)ys[oy + 2] * nx + xs[ox + 2]];
-    }
-};
-
-// One Runge-Kutta stage without fusion, with the same per-cell arithmetic
-// as the fused step:
-//   STAGE2 == false:  out = f + dt L(f)
-//   STAGE2 == true:   out = base / 2 + (f + dt L(f)) / 2
-template <typename S, bool STAGE2>
-__global__ void __launch_bounds__(256) k_stage(const S* __restrict__ fin, const S* __restrict__ base,
-                                               S* __restrict__ fout,
-                                               const KParams* __restrict__ Kd) {
-    const KParams& K = *Kd;
-    const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (x >= K.nx || y >= K.ny) return;
-    const int64_t cells = (int64_t)K.nx * K.ny;
-    GlobalLd<S> ld;
-    ld.f = fin;
-    ld.cells = cells;
-    ld.nx = K.nx;
-#pragma unroll
-    for (int o = -2; o <= 2; ++o) {
-        ld.xs[o + 2] = wrap_or_clamp(x + o, K.nx, K.bcx);
-        ld.ys[o + 2] = wrap_or_clamp(y + o, K.ny, K.bcy);
-    }
-    S out[NV];
-    stage_cell_k<S, STAGE2>(ld, K, out);
-    const int64_t c = (int64_t)y * K.nx + x;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        S v = out[i];
-        if (STAGE2) v = fma(S(0.5), base[i * cells + c], v);
-        fout[i * cells + c] = v;
-    }
-}
-
-// One Runge-Kutta stage of the compensated form, one cell per thread: f is
-// read from float storage and every term is formed in double, as in the
-// FP64 form:
-//   STAGE2 == false:  y = f + A,              out = round(y + C),
-//                     r_out = r + m(y - out)
-//   STAGE2 == true:   y = base/2 + f/2 + A,   out = round(y + C),
-//                     r_out = r_base/2 + r/2 + m(y - out)
-// where A is the stage's advection term dt (-v . grad f) of Eqs. (12)-(20)
-// and C its relaxation term -dt (f - f^eq)/tau of Eq. (1) (both halved in
-// the second stage), f^eq is that of the compensated moments m(f) + r, and
-// m(.) is (rho, j_x, j_y, 2E) of a set of 16 values.  The conserved moments
-// m(f) + r of the output are those of the stage's combination without C
-// (the advection flux changes them, the relaxation does not); C itself
-// carries dt/tau of r into f.  The differences of the NND stencil are exact
-// in double (two floats of like size), so the advection terms of
-// neighbouring cells cancel in the grid sums to FP64 rounding.
-template <bool STAGE2>
-__global__ void __launch_bounds__(256) k_stage_comp(const float* __restrict__ fin,
-                                                    const float* __restrict__ base,
-                                                    float* __restrict__ fout,
-                                                    const KParams* __restrict__ Kd) {
-    const KParams& K = *Kd;
-    const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (x >= K.nx || y >= K.ny) return;
-    const int64_t cells = (int64_t)K.nx * K.ny;
-    GlobalLd<float> ld;
-    ld.f = fin;
-    ld.cells = cells;
-    ld.nx = K.nx;
-#pragma unroll
-    for (int o = -2; o <= 2; ++o) {
-        ld.xs[o + 2] = wrap_or_clamp(x + o, K.nx, K.bcx);
-        ld.ys[o + 2] = wrap_or_clamp(y + o, K.ny, K.bcy);
-    }
-    const int64_t c = (int64_t)y * K.nx + x;
-    // The loads of a cell's 16 values and residual, and then of each group's
-    // stencils, are issued together and held by one empty asm statement
-    // before any is used: left to itself the compiler fetched one value at a
-    // time (load, wait, convert) to save registers, and the stage took twice
-    // as long.
-    float f[NV + 4];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) f[i] = ld(i, 0, 0);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) f[NV + k] = fin[(NV + k) * cells + c];
-    hold_values(f);
-    double fd[NV], r[4];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) fd[i] = (double)f[i];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) r[k] = (double)f[NV + k];
-    Parity g;
-    to_parity(fd, g);
-    const Macro m = macro_compensated(g, r, K);
-    double neq[NV];
-    nonequilibrium(g, m, K, K.a, neq);
-    const double nza = K.nzq[STAGE2][0], nzd = K.nzq[STAGE2][1];
-    double lost[NV];
-    // groups of four velocities (axis group: one stencil direction each,
-    // diagonal group: two); st[k][0..2] the x stencil of velocity i0 + k
-    // without its centre, st[k][3..5] the y stencil, upwind first
-#pragma unroll
-    for (int i0 = 0; i0 < NV; i0 += 4) {
-        float st[4][6];
-        float hb[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int i = i0 + k;
-            if (SX[i] > 0) {
-                st[k][0] = ld(i, -2, 0); st[k][1] = ld(i, -1, 0); st[k][2] = ld(i, 1, 0);
-            } else if (SX[i] < 0) {
-                st[k][0] = ld(i, -1, 0); st[k][1] = ld(i, 1, 0); st[k][2] = ld(i, 2, 0);
-            } else {
-                st[k][0] = st[k][1] = st[k][2] = 0.0f;
-            }
-            if (SY[i] > 0) {
-                st[k][3] = ld(i, 0, -2); st[k][4] = ld(i, 0, -1); st[k][5] = ld(i, 0, 1);
-            } else if (SY[i] < 0) {
-                st[k][3] = ld(i, 0, -1); st[k][4] = ld(i, 0, 1); st[k][5] = ld(i, 0, 2);
-            } else {
-                st[k][3] = st[k][4] = st[k][5] = 0.0f;
-            }
-            hb[k] = STAGE2 ? base[i * cells + c] : 0.0f;
-        }
-        hold_values(st);
-        if (STAGE2) hold_values(hb);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int i = i0 + k;
-            const double cx = STAGE2 ? K.cxh[i] : K.cx[i];
-            const double cy = STAGE2 ? K.cyh[i] : K.cy[i];
-            double adv = 0.0;
-            if (SX[i] > 0)
-                adv = cx * nnd_pos<double>(st[k][0], st[k][1], fd[i], st[k][2]);
-            else if (SX[i] < 0)
-                adv = cx * nnd_neg<double>(st[k][0], fd[i], st[k][1], st[k][2]);
-            if (SY[i] > 0)
-                adv += cy * nnd_pos<double>(st[k][3], st[k][4], fd[i], st[k][5]);
-            else if (SY[i] < 0)
-                adv += cy * nnd_neg<double>(st[k][3], fd[i], st[k][4], st[k][5]);
-            const double coll = ((i & 4) ? nzd : nza) * neq[i];
-            double yv = adv;
-            if (STAGE2) yv += 0.5 * fd[i] + 0.5 * (double)hb[k];
-            else yv += fd[i];
-            const float o = (float)(yv + coll);
-            fout[i * cells + c] = o;
-            lost[i] = yv - (double)o;
-        }
-    }
-    Parity gl;
-    to_parity(lost, gl);
-    double dm[4];
-    conserved_of(gl, K, dm);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        double rk = r[k];
-        if (STAGE2) rk = 0.5 * (double)base[(NV + k) * cells + c] + 0.5 * rk;
-        fout[(NV + k) * cells + c] = (float)(rk + dm[k]);
-    }
-}
-
 inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
 }  // namespace
@@ -486,19 +296,6 @@ hipError_t launch_sum_partials(const double* part, int nblocks, int ncomp, doubl
     return hipGetLastError();
 }
 
-template <typename S>
-hipError_t launch_stage(const void* fin, const void* base, void* fout, bool stage2,
-                        const KParams& K, const KParams* Kd, hipStream_t st) {
-    const dim3 grid(blocks_for(K.nx, 64), blocks_for(K.ny, 4));
-    if (stage2)
-        hipLaunchKernelGGL((k_stage<S, true>), grid, dim3(256), 0, st, (const S*)fin,
-                           (const S*)base, (S*)fout, Kd);
-    else
-        hipLaunchKernelGGL((k_stage<S, false>), grid, dim3(256), 0, st, (const S*)fin,
-                           (const S*)base, (S*)fout, Kd);
-    return hipGetLastError();
-}
-
 hipError_t launch_init_comp(const double* rho, const double* ux, const double* uy,
                             const double* T, void* f, const KParams& K, hipStream_t st) {
     const int64_t cells = (int64_t)K.nx * K.ny;
@@ -536,18 +333,6 @@ hipError_t launch_totals_comp(const void* f, double* partials, int nblocks, doub
     return hipGetLastError();
 }
 
-hipError_t launch_stage_comp(const void* fin, const void* base, void* fout, bool stage2,
-                             const KParams& K, const KParams* Kd, hipStream_t st) {
-    const dim3 grid(blocks_for(K.nx, 64), blocks_for(K.ny, 4));
-    if (stage2)
-        hipLaunchKernelGGL((k_stage_comp<true>), grid, dim3(256), 0, st, (const float*)fin,
-                           (const float*)base, (float*)fout, Kd);
-    else
-        hipLaunchKernelGGL((k_stage_comp<false>), grid, dim3(256), 0, st, (const float*)fin,
-                           (const float*)base, (float*)fout, Kd);
-    return hipGetLastError();
-}
-
 #define CDBM_INSTANTIATE(S)                                                                     \
     template hipError_t launch_init<S>(const double*, const double*, const double*,            \
                                        const double*, void*, const KParams&, hipStream_t);     \
@@ -555,9 +340,7 @@ hipError_t launch_stage_comp(const void* fin, const void* base, void* fout, bool
                                           const KParams&, hipStream_t);                        \
     template hipError_t launch_tne<S>(const void*, double*, bool, const KParams&, hipStream_t);      \
     template hipError_t launch_totals<S>(const void*, double*, int, double*, const KParams&,   \
-                                         hipStream_t);                                         \
-    template hipError_t launch_stage<S>(const void*, const void*, void*, bool, const KParams&, \
-                                        const KParams*, hipStream_t);
+                                         hipStream_t);
 CDBM_INSTANTIATE(float)
 CDBM_INSTANTIATE(double)
 #undef CDBM_INSTANTIATE

@@ -26,7 +26,7 @@ hipError_t launch_sum_partials(const double* part, int nblocks, int ncomp, doubl
                                hipStream_t st);
 template <typename S>
 hipError_t launch_stage(const void* fin, const void* base, void* fout, bool stage2,
-                        const KParams& K, const KParams* Kd, hipStream_t st);
+                        const KParams& K, const StageParams* Kd, hipStream_t st);
 
 // The compensated mixed form (CDBM_MIXED_COMP): float states of 20 planes,
 // the 16 of f and the four of the conserved-moment residual r.
@@ -39,7 +39,7 @@ hipError_t launch_tne_comp(const void* f, double* out12, bool raw, const KParams
 hipError_t launch_totals_comp(const void* f, double* partials, int nblocks, double* out4,
                               const KParams& K, hipStream_t st);
 hipError_t launch_stage_comp(const void* fin, const void* base, void* fout, bool stage2,
-                             const KParams& K, const KParams* Kd, hipStream_t st);
+                             const KParams& K, const StageParams* Kd, hipStream_t st);
 
 // Compute units of the current device (cached per device; 256 if the query
 // fails).

@@ -222,6 +222,22 @@ int build_params(const cdbm_params& p, KParams& k, std::string& err) {
     if ((rc = block(6, ree, cee, see, &k.iee[0][0], "even-even")) != CDBM_OK) return rc;
     if ((rc = block(4, roe, coe, soe, &k.ioe[0][0], "odd-even")) != CDBM_OK) return rc;
     if ((rc = block(4, reo, ceo, soe, &k.ieo[0][0], "even-odd")) != CDBM_OK) return rc;
+    // the x <-> y symmetry maps one odd block to the other (moments 2 <-> 3);
+    // the inversion keeps that up to the last bit, and from here it is exact
+    {
+        double scale = 0.0;
+        for (int r = 0; r < 4; ++r)
+            for (int c = 0; c < 4; ++c) scale = std::fmax(scale, std::fabs(k.ioe[r][c]));
+        static const int swap[4] = {0, 1, 3, 2};
+        for (int r = 0; r < 4; ++r)
+            for (int c = 0; c < 4; ++c) {
+                if (!(std::fabs(k.ieo[r][c] - k.ioe[r][swap[c]]) <= 1e-12 * scale)) {
+                    err = "internal: odd blocks are not images under x <-> y";
+                    return CDBM_EINVAL;
+                }
+                k.ieo[r][c] = k.ioe[r][swap[c]];
+            }
+    }
     if ((rc = block(2, roo, coo, soo, &k.ioo[0][0], "odd-odd")) != CDBM_OK) return rc;
 
     // Mirror form of the even-even block (KParams::eep, ees); the x <-> y
@@ -292,6 +308,33 @@ int build_params(const cdbm_params& p, KParams& k, std::string& err) {
     k.bcx = p.bc_x;
     k.bcy = p.bc_y;
     return CDBM_OK;
+}
+
+void build_stage(const KParams& k, StageParams& m) {
+    std::memset(&m, 0, sizeof(m));
+    static const int en[4] = {0, 2, 3, 5};
+    for (int g = 0; g < 4; ++g) {
+        m.jv[g] = k.jx[g];
+        m.en[g] = k.en[en[g]];
+        for (int h = 0; h < 2; ++h) {
+            // velocities 0, 4, 8, 12 move towards larger x, 1, 4, 9, 12 towards larger y
+            const int ix = 4 * g, iy = 4 * g + (g % 2 == 0 ? 1 : 0);
+            m.cd[h][g] = h ? k.cxh[ix] : k.cx[ix];
+            m.cd[h][4 + g] = h ? k.cyh[iy] : k.cy[iy];
+            m.cf[h][g] = h ? k.cxhf[ix] : k.cxf[ix];
+            m.cf[h][4 + g] = h ? k.cyhf[iy] : k.cyf[iy];
+            if (g < 2) {
+                m.cd[h][8 + g] = k.nzq[h][g];
+                m.cf[h][8 + g] = k.nzqf[h][g];
+            }
+        }
+        for (int c = 0; c < 4; ++c) m.ioe[g][c] = k.ioe[g][c];
+    }
+    m.inv_a = k.inv_a;
+    m.a = k.a;
+    std::memcpy(m.eep, k.eep, sizeof(m.eep));
+    std::memcpy(m.ees, k.ees, sizeof(m.ees));
+    std::memcpy(m.ioo, k.ioo, sizeof(m.ioo));
 }
 
 void build_quad(const KParams& k, QuadParams& r) {

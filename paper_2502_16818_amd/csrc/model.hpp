@@ -37,7 +37,8 @@ constexpr int SY[NV] = {0, 1, 0, -1, 1, 1, -1, -1, 0, 1, 0, -1, 1, 1, -1, -1};
 struct KParams {
     // Inverses of the parity blocks of M0.  Output rows are pre-multiplied by
     // 1/2 (axis groups) or 1/4 (diagonal groups), so that the unpacking of
-    // parity combinations into the 16 distributions is additions only.
+    // parity combinations into the 16 distributions is additions only.  ieo is
+    // ioe with columns 2 and 3 swapped (the x <-> y symmetry, exactly).
     double iee[6][6];
     double ioe[4][4];
     double ieo[4][4];
@@ -99,6 +100,22 @@ struct alignas(64) QuadParams {
 static_assert(sizeof(QuadParams::Lane) == 5 * 64 && sizeof(QuadParams::Shared) == 5 * 64,
               "quad_const() touches each 64-byte line");
 
+// The constants of a stage with one cell per lane (kernels_stage.hip), packed
+// in the order of use, so that they come in a few wide scalar loads: the
+// groups' speeds (the rows of both momenta), the energy row, 1 / (D + I),
+// D + I, then eep, ees, ioo and ioe (ieo is its mirror image); for the two
+// Runge-Kutta stages the NND coefficients of velocities towards larger indices
+// (groups a .. d along x, then along y) and the relaxation factors of the axis
+// and the diagonal groups.
+struct alignas(64) StageParams {
+    double jv[4], en[4];
+    double inv_a, a, eep[2][6], ees[2][4], ioo[2][2];
+    double ioe[4][4];
+    double cd[2][10];
+    float cf[2][10];
+};
+
+void build_stage(const KParams& k, StageParams& m);
 void build_quad(const KParams& k, QuadParams& q);
 
 // Validate p and fill k.  Returns CDBM_OK or an error code with a message.
