@@ -5,19 +5,22 @@
 // Eqs. (12)-(20)).  Its transpose applied to a vector a at cell y is
 //   a_i + dt (J_adv^T a)_i - (dt/tau) (a_i - [(d g^eq / d g)^T a]_i).
 //
-// NND transpose.  With the minmod selections fixed, D is linear.  The face
-// selection s(x) = (alpha, beta) of minmod(d(x+1/2), d(x-1/2)) (alpha: the
-// first argument is taken, beta: the second, neither: 0) follows the branch
-// order of Eq. (16): zero if the differences do not share a strict sign,
-// else the first argument when |X| <= |Y|.  For v > 0
-//   D(x) = d(x-1/2) + (mm(x) - mm(x-1)) / 2,  mm(x) = minmod(d(x+1/2), d(x-1/2)),
-// so dD(x)/df(x+k) for k = +1, 0, -1, -2 is
-//   a(x)/2,  1 + (b(x) - a(x-1) - a(x))/2,  -1 - (b(x) - a(x-1) + b(x-1))/2,  b(x-1)/2
-// and for v < 0, D(x) = d(x+1/2) - (mm(x+1) - mm(x)) / 2 gives for k = +2..-1
-//   -a(x+1)/2,  1 + (a(x+1) - b(x+1) + a(x))/2,  -1 + (b(x+1) - a(x) + b(x))/2,  -b(x)/2.
-// The transpose gathers, at an extended position p, sum_k coef_k(p-k) a(p-k)
-// over real cells p-k.  Ghost positions of a zero-gradient side alias the
-// edge cell, so their gathers are added to it; periodic positions wrap.
+// NND transpose.  With the minmod selections fixed, D is linear.  The
+// selection at a cell is (alpha, beta): mm(x) = alpha d(x+1/2) + beta d(x-1/2)
+// (branch order of Eq. (16): neither if the differences do not share a strict
+// sign, else the first argument when |X| <= |Y|).  For v > 0
+//   D(x) = d(x-1/2) + (mm(x) - mm(x-1)) / 2,
+// so with a the adjoint of D the adjoint of mm(x) is (a(x) - a(x+1)) / 2 and
+// that of the face difference d(x+1/2)
+//   G(x+1/2) = a(x+1) + alpha(x) (a(x) - a(x+1)) / 2
+//                     + beta(x+1) (a(x+1) - a(x+2)) / 2;
+// for v < 0, D(x) = d(x+1/2) - (mm(x+1) - mm(x)) / 2 gives
+//   G(x+1/2) = a(x) + alpha(x) (a(x) - a(x-1)) / 2 + beta(x+1) (a(x+1) - a(x)) / 2.
+// As d(x+1/2) = f(x+1) - f(x), the transpose at x is G(x-1/2) - G(x+1/2).
+// Periodic positions wrap.  At a zero-gradient side a is zero at the ghosts,
+// and the ghosts' own contributions belong to the edge cell, whose values they
+// repeat: their sum telescopes to minus G of the grid's edge face, so that
+// face simply drops out.
 //
 // Equilibrium transpose.  f^eq = P h with h = rho B mhat(u, T) (P: unpacking
 // of parity combinations, B: scaled block inverses).  P^T is the parity
@@ -32,49 +35,6 @@
 #include "cell.hpp"
 
 namespace cdbm {
-
-// Parity form h of f^eq (f^eq = unpacking of h, see equilibrium()).
-__device__ __forceinline__ void equilibrium_parity(const Macro& m, const KParams& K, double a,
-                                                   Parity& h) {
-    const double ux = m.ux, uy = m.uy, T = m.T;
-    const double ux2 = ux * ux, uy2 = uy * uy, u2 = ux2 + uy2, uxy = ux * uy;
-    const double aT = a * T;
-    const double A2 = u2 + aT + 2.0 * T;
-    const double A4 = A2 + 2.0 * T;
-    const double mee[6] = {1.0, u2 + aT, ux2 + T, uy2 + T, ux2 * A4 + T * A2, uy2 * A4 + T * A2};
-    const double moe[4] = {ux, ux * A2, ux * (ux2 + 3.0 * T), ux * (uy2 + T)};
-    const double meo[4] = {uy, uy * A2, uy * (ux2 + T), uy * (uy2 + 3.0 * T)};
-    const double moo[2] = {uxy, uxy * A4};
-#pragma unroll
-    for (int r = 0; r < 6; ++r) {
-        double s = K.iee[r][0];
-#pragma unroll
-        for (int c = 1; c < 6; ++c) s = fma(K.iee[r][c], mee[c], s);
-        h.ee[r] = m.rho * s;
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        double so = 0.0, se = 0.0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            so = fma(K.ioe[r][c], moe[c], so);
-            se = fma(K.ieo[r][c], meo[c], se);
-        }
-        h.oe[r] = m.rho * so;
-        h.eo[r] = m.rho * se;
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) h.oo[r] = m.rho * fma(K.ioo[r][0], moo[0], K.ioo[r][1] * moo[1]);
-}
-
-// Minmod selection of Eq. (16) as (alpha, beta) in {0, 1}.
-template <typename R>
-__device__ __forceinline__ void minmod_select(R X, R Y, double& alpha, double& beta) {
-    const bool same = (X > R(0) && Y > R(0)) || (X < R(0) && Y < R(0));
-    const bool first = fabs((double)X) <= fabs((double)Y);
-    alpha = (same && first) ? 1.0 : 0.0;
-    beta = (same && !first) ? 1.0 : 0.0;
-}
 
 struct Quad {
     double rho, ux, uy, T;
@@ -182,88 +142,93 @@ __device__ __forceinline__ double moments_vjp_k(const Macro& m, const KParams& K
     return g.rho + (g.ux * cx + g.uy * cy + g.T * (e - a * m.T) / a) / m.rho;
 }
 
-// The transposes read one velocity's state and adjoint along a line (x or y)
-// through the cell, at offsets -3 .. 3 for the state and -2 .. 2 for the
-// adjoint, held in registers.  Positions are offsets from the cell (local
-// position 0); the global index of a position only decides which gathers a
-// zero-gradient side skips.  Face selections: bit 0 alpha, bit 1 beta of
-// minmod(F(l+1) - F(l), F(l) - F(l-1)) along the line (Eq. (16) branch
-// order), at offsets -2 .. 2.  Offsets outside -2 .. 2 occur only in gathers
-// that a zero-gradient side skips; they are clamped to keep every index in
-// the arrays.
-__device__ __forceinline__ constexpr int line_slot(int l) {
-    return (l < -2 ? -2 : (l > 2 ? 2 : l)) + 2;
-}
-struct RegSel {
-    unsigned char c[5];
-    __device__ __forceinline__ void at(int l, double& al, double& be) const {
-        const int k = c[line_slot(l)];
-        al = (double)(k & 1);
-        be = (double)(k >> 1);
-    }
-};
-struct RegLine {
-    double v[5];   // the adjoint, zero at zero-gradient ghosts
-    __device__ __forceinline__ double at(int l) const { return v[line_slot(l)]; }
-};
-
-template <typename S>
-__device__ __forceinline__ unsigned char face_code(S fm, S f0, S fp) {
-    double al, be;
-    minmod_select<S>(fp - f0, f0 - fm, al, be);
-    return (unsigned char)((al != 0.0 ? 1 : 0) | (be != 0.0 ? 2 : 0));
-}
-
-// Gather of the NND transpose at local position lp, global position gp
-// (see the header).
-template <bool POS>
-__device__ __forceinline__ double nnd_gather(const RegSel& Sl, const RegLine& A, int lp, int gp,
-                                             int n, int bc) {
-    double acc = 0.0;
+// Parity form h of f^eq (f^eq = unpacking of h, see equilibrium()), from the
+// whole block inverses, the products in one fixed order of rounding: dL/dtau
+// sums a . (g - f^eq), where nearly all of a . g cancels when a is close to a
+// moment (conserved), so the form must round like its own earlier values.
+template <typename Table>
+__device__ __forceinline__ void equilibrium_parity(const Macro& m, Table& K, double a, Parity& h) {
+    const double ux = m.ux, uy = m.uy, T = m.T;
+    const double ux2 = ux * ux, uy2 = uy * uy, u2 = fma(ux, ux, uy2), uxy = ux * uy;
+    const double E = fma(a, T, u2), A2 = fma(2.0, T, E), A4 = fma(2.0, T, A2);
+    const double xx = fma(ux, ux, T), yy = fma(uy, uy, T), TA2 = T * A2;
+    const double mee[6] = {1.0, E, xx, yy, fma(ux2, A4, TA2), fma(uy2, A4, TA2)};
+    const double moe[4] = {ux, ux * A2, ux * fma(3.0, T, ux2), ux * yy};
+    const double meo[4] = {uy, uy * A2, uy * xx, uy * fma(3.0, T, uy2)};
+    const double moo[2] = {uxy, uxy * A4};
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        const int k = POS ? 1 - kk : 2 - kk;
-        const int gx = gp - k;
-        if (bc != CDBM_PERIODIC && (gx < 0 || gx >= n)) continue;
-        const int l = lp - k;
-        double coef;
-        if (POS) {
-            double a0, b0, a1, b1;   // s(l-1), s(l)
-            Sl.at(l - 1, a0, b0);
-            Sl.at(l, a1, b1);
-            if (k == 1) coef = 0.5 * a1;
-            else if (k == 0) coef = 1.0 + 0.5 * (b1 - a0 - a1);
-            else if (k == -1) coef = -1.0 - 0.5 * (b1 - a0 + b0);
-            else coef = 0.5 * b0;
-        } else {
-            double a1, b1, a2, b2;   // s(l), s(l+1)
-            Sl.at(l, a1, b1);
-            Sl.at(l + 1, a2, b2);
-            if (k == 2) coef = -0.5 * a2;
-            else if (k == 1) coef = 1.0 + 0.5 * (a2 - b2 + a1);
-            else if (k == 0) coef = -1.0 + 0.5 * (b2 - a1 + b1);
-            else coef = -0.5 * b1;
-        }
-        acc = fma(coef, A.at(l), acc);
+    for (int r = 0; r < 6; ++r) {
+        double s = K.iee[r][0];
+#pragma unroll
+        for (int c = 1; c < 6; ++c) s = fma(K.iee[r][c], mee[c], s);
+        h.ee[r] = m.rho * s;
     }
-    return acc;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        double so = 0.0, se = 0.0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            so = fma(K.ioe[r][c], moe[c], so);
+            se = fma(K.ieo[r][c], meo[c], se);
+        }
+        h.oe[r] = m.rho * so;
+        h.eo[r] = m.rho * se;
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) h.oo[r] = m.rho * fma(K.ioo[r][0], moo[0], K.ioo[r][1] * moo[1]);
 }
 
-// Full NND transpose at the real cell of local position lc, global position
-// gc, with the ghost aliases of a zero-gradient side folded in.
-template <bool POS>
-__device__ __forceinline__ double nnd_transpose(const RegSel& Sl, const RegLine& A, int lc, int gc,
-                                                int n, int bc) {
-    double acc = nnd_gather<POS>(Sl, A, lc, gc, n, bc);
-    if (bc == CDBM_ZERO_GRADIENT) {
-        if (gc == 0)
-            acc += nnd_gather<POS>(Sl, A, lc - 1, -1, n, bc) +
-                   nnd_gather<POS>(Sl, A, lc - 2, -2, n, bc);
-        if (gc == n - 1)
-            acc += nnd_gather<POS>(Sl, A, lc + 1, n, n, bc) +
-                   nnd_gather<POS>(Sl, A, lc + 2, n + 1, n, bc);
+// Half the minmod selections at a cell, from the differences X on its far side
+// and Y on its near side (the branch order of Eq. (16)): alpha / 2 (X is
+// taken: the signs agree and 0 < |X| <= |Y|) and beta / 2 (Y is taken:
+// 0 < |Y| < |X|).  With Ys = Y times the sign of X these are 0 < |X| <= Ys and
+// 0 < Ys < |X|; a NaN selects neither.
+__device__ __forceinline__ float times_sign(float y, float x) {
+    return __int_as_float(__float_as_int(y) ^ (__float_as_int(x) & (int)0x80000000));
+}
+__device__ __forceinline__ double times_sign(double y, double x) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, y);
+    const uint32_t s = (uint32_t)(__builtin_bit_cast(uint64_t, x) >> 32) & 0x80000000u;
+    return __builtin_bit_cast(double, b ^ ((uint64_t)s << 32));
+}
+// 0.5 or 0.0 (the low word of both is zero: one select).
+__device__ __forceinline__ double half_if(bool c) {
+    return __builtin_bit_cast(double, (uint64_t)(c ? 0x3fe00000u : 0u) << 32);
+}
+template <typename S>
+__device__ __forceinline__ double half_alpha(S X, S Y) {
+    const S ax = fabs(X), ys = times_sign(Y, X);
+    return half_if(ax > S(0) && ax <= ys);
+}
+template <typename S>
+__device__ __forceinline__ double half_beta(S X, S Y) {
+    const S ax = fabs(X), ys = times_sign(Y, X);
+    return half_if(ys > S(0) && ys < ax);
+}
+
+// Transpose of the flux difference along a line at cell x (without its
+// coefficient), from the state f(x-2 .. x+2) and the adjoint of the
+// differences at x-2 .. x+2 (those not needed are not read), through the
+// adjoints G of the face differences d (see the header): km and kp are 0 where
+// the face on that side is the edge of a zero-gradient side, else 1.
+template <bool POS, typename S>
+__device__ __forceinline__ double nnd_transpose(const S f[5], const double A[5], double km,
+                                                double kp) {
+    const S d0 = f[1] - f[0], d1 = f[2] - f[1], d2 = f[3] - f[2], d3 = f[4] - f[3];
+    const double am = half_alpha(d1, d0);                           // cell x - 1
+    const double ac = half_alpha(d2, d1), bc = half_beta(d2, d1);   // cell x
+    const double bp = half_beta(d3, d2);                            // cell x + 1
+    double gm, gp;   // faces x - 1/2, x + 1/2
+    if (POS) {
+        const double e = A[1] - A[2], h = A[2] - A[3], k = A[3] - A[4];
+        gm = fma(am, e, fma(bc, h, A[2]));
+        gp = fma(ac, h, fma(bp, k, A[3]));
+    } else {
+        const double e = A[1] - A[0], h = A[2] - A[1], k = A[3] - A[2];
+        gm = fma(am, e, fma(bc, h, A[1]));
+        gp = fma(ac, h, fma(bp, k, A[2]));
     }
-    return acc;
+    return fma(-kp, gp, km * gm);
 }
 
 }  // namespace cdbm

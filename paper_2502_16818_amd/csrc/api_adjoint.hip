@@ -41,9 +41,11 @@ int step_adjoint_impl(cdbm_handle* h, const void* f_n, const void* f1, const voi
     const bool defer = dtau == nullptr;
     double* part2 = defer ? h->tau_acc : h->tau_part;
     double* part1 = defer ? h->tau_acc : h->tau_part + nb;
-    e = launch_stage_adjoint<S>(f1, lam_np1, nullptr, h->lam_mid, part2, defer, 0.5, 0.0, K, st);
+    e = launch_stage_adjoint<S>(f1, lam_np1, nullptr, h->lam_mid, part2, defer, 0.5, 0.0, K,
+                                h->sdev, h->kdev, st);
     if (e != hipSuccess) return hip_fail(e, "stage adjoint launch");
-    e = launch_stage_adjoint<S>(f_n, h->lam_mid, lam_np1, lam_n, part1, defer, 1.0, 0.5, K, st);
+    e = launch_stage_adjoint<S>(f_n, h->lam_mid, lam_np1, lam_n, part1, defer, 1.0, 0.5, K,
+                                h->sdev, h->kdev, st);
     if (e != hipSuccess) return hip_fail(e, "stage adjoint launch");
     if (defer) return CDBM_OK;
     e = launch_accumulate_scalar(h->tau_part, 2 * nb, h->tau_part + 2 * nb, 1.0, dtau, false, st);

@@ -249,4 +249,21 @@ __device__ __forceinline__ int wrap_or_clamp(int i, int n, int bc) {
     return i < 0 ? 0 : (i >= n ? n - 1 : i);
 }
 
+// Position of block b of n in a numbering whose consecutive blocks run on one
+// XCD: the hardware hands blocks to the eight XCDs in turn, each with an L2 of
+// its own, so blocks that share rows have to be eight apart to share a cache.
+__device__ __forceinline__ uint32_t band_index(uint32_t b, uint32_t n) {
+    const uint32_t per = n / 8;
+    return b < 8 * per ? (b % 8) * per + b / 8 : b;
+}
+
+// wrap_or_clamp for an index at most 2 off the grid.
+__device__ __forceinline__ int wrap_by_two(int i, int n, bool periodic) {
+    if (periodic) {
+        if (n == 1) return 0;
+        return i < 0 ? i + n : (i >= n ? i - n : i);
+    }
+    return min(max(i, 0), n - 1);
+}
+
 }  // namespace cdbm

@@ -9,175 +9,409 @@ namespace cdbm {
 
 namespace {
 
-// out = w_add * add + w_in * E'(g)^T a, and the per-block partial sums of
+typedef const __attribute__((address_space(4))) StageParams* AdjointTable;
+typedef const __attribute__((address_space(4))) KParams* BlockTable;
+
+// Reads of one vector at the lane's column: rows y - 2 .. y + 2 are scalar byte
+// offsets in a plane, the column a vector one.  Reads out of a plane's bounds
+// give 0: a column offset of OUTSIDE is the adjoint at a zero-gradient ghost.
+constexpr uint32_t OUTSIDE = 0x80000000u;
+template <typename T>
+struct ColumnLd {
+    const char* p;
+    int64_t plane;       // bytes of a plane (at most 2^31)
+    uint32_t row[5];
+    uint32_t col[5];     // the lane's column in those rows (OUTSIDE for a ghost)
+    __device__ __forceinline__ T operator()(int i, int o) const {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char*>(p) + i * plane, 0, (int)(uint32_t)plane, 0x00020000);
+        const int v = (int)col[o + 2], s = (int)row[o + 2];
+        if constexpr (sizeof(T) == 4) {
+            return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, v, s, 0));
+        } else {
+            typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+            const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rs, v, s, 0);
+            return __builtin_bit_cast(double, w);
+        }
+    }
+};
+
+// GHOSTS_ZERO: ghosts of zero-gradient sides read 0 (else the edge cell).
+template <bool GHOSTS_ZERO, typename T>
+__device__ __forceinline__ void column_offsets(ColumnLd<T>& ld, const void* f, int x, int y,
+                                               int nx, int ny, int bc) {
+    ld.p = (const char*)f;
+    ld.plane = (int64_t)nx * ny * (int64_t)sizeof(T);
+    const bool px = !(bc & 1), py = !(bc & 2);
+    const int cx = x < nx ? x : wrap_or_clamp(x, nx, bc & 1);
+    const bool gx = GHOSTS_ZERO && !px && x >= nx;
+#pragma unroll
+    for (int o = -2; o <= 2; ++o) {
+        const int cy = wrap_by_two(y + o, ny, py);
+        const bool gy = GHOSTS_ZERO && !py && cy != y + o;
+        ld.row[o + 2] = (uint32_t)cy * (uint32_t)nx * (uint32_t)sizeof(T);
+        ld.col[o + 2] = gx || gy ? OUTSIDE : (uint32_t)cx * (uint32_t)sizeof(T);
+    }
+}
+
+// Velocities of a part with a component along x, in order, and the position of
+// velocity i among them (three of every four: the axis groups have two, the
+// diagonal ones four).
+constexpr int x_slot(int i) { return (i / 8) * 6 + ((i / 4) % 2 == 0 ? (i % 4) / 2 : 2 + i % 4); }
+constexpr int x_velocity(int k) { return (k / 6) * 8 + (k % 6 < 2 ? 2 * (k % 6) : 2 + k % 6); }
+static_assert(x_slot(0) == 0 && x_slot(2) == 1 && x_slot(4) == 2 && x_slot(15) == 11 &&
+                  x_velocity(1) == 2 && x_velocity(2) == 4 && x_velocity(11) == 15,
+              "velocities 0, 2, 4 .. 7, 8, 10, 12 .. 15");
+
+// The two columns on either side of a wave's 64 columns, for the x differences
+// of all its velocities in one load: lane 4 k + h takes column h (-2, -1, 64,
+// 65) of the k-th velocity with a component along x.
+constexpr int NX = 6;   // those of a part
+template <bool GHOSTS_ZERO, typename T>
+__device__ __forceinline__ T halo_value(const void* f, int k0, int x0, int y, int nx, int ny,
+                                        int bc) {
+    const int lane = threadIdx.x & 63, h = lane & 3;
+    const int k = min(lane >> 2, NX - 1);
+    const int x = x0 + (h < 2 ? h - 2 : 62 + h), cx = wrap_or_clamp(x, nx, bc & 1);
+    const int i = x_velocity(k0 + k);
+    const T v = ((const T*)f)[((int64_t)i * ny + y) * nx + cx];
+    return GHOSTS_ZERO && (bc & 1) && cx != x ? T(0) : v;
+}
+
+// One velocity's y stencils without the centres: the state at offsets -2 .. 2
+// and the adjoint at the three of them its transpose reads.
+template <typename S>
+struct AdjointStencil {
+    S f[5];
+    double a[5];
+};
+template <typename S>
+__device__ __forceinline__ void load_adjoint_stencil(ColumnLd<S> g, ColumnLd<double> a, int i,
+                                                     AdjointStencil<S>& s) {
+    if (SY[i] == 0) return;
+    // descriptors formed anew: kept from the loads of the centres, those of 16
+    // planes of both vectors would fill the scalar registers
+    const uint32_t z0 = (uint32_t)opaque_zero();
+    g.p += z0;
+    a.p += z0;
+#pragma unroll
+    for (int o = -2; o <= 2; ++o) {
+        if (o == 0) continue;
+        s.f[o + 2] = g(i, o);
+        // v > 0 reads the adjoint at -1, 1, 2 and v < 0 at -2, -1, 1
+        s.a[o + 2] = (o != (SY[i] > 0 ? -2 : 2)) ? a(i, o) : 0.0;
+    }
+}
+
+// Parity combinations of groups 2 q and 2 q + 1 (v: their eight values).
+__device__ __forceinline__ void half_parity(const double v[8], double c[8]) {
+    c[0] = v[0] + v[2];
+    c[1] = v[1] + v[3];
+    c[2] = v[0] - v[2];
+    c[3] = v[1] - v[3];
+    const double s01 = v[4] + v[5], s23 = v[6] + v[7];
+    const double d01 = v[4] - v[5], d23 = v[6] - v[7];
+    c[4] = s01 + s23;
+    c[5] = d01 - d23;
+    c[6] = s01 - s23;
+    c[7] = d01 + d23;
+}
+__device__ __forceinline__ void set_half(Parity& g, int q, const double c[8]) {
+    g.ee[3 * q] = c[0];
+    g.ee[3 * q + 1] = c[1];
+    g.ee[3 * q + 2] = c[4];
+    g.oe[2 * q] = c[2];
+    g.oe[2 * q + 1] = c[5];
+    g.eo[2 * q] = c[3];
+    g.eo[2 * q + 1] = c[6];
+    g.oo[q] = c[7];
+}
+
+// The equilibrium transpose of a cell as a polynomial in the velocity:
+// [(d g^eq / d g)^T a]_i = c0 + cx v_ix + cy v_iy + ce (|v_i|^2 + eta_i^2).
+struct EqTranspose {
+    double c0, cx, cy, ce;
+};
+
+// From the state m and pa = P^T a: w = B^T pa (the even-even block in mirror
+// form, see nonequilibrium()) and its products with the raw moments and their
+// derivatives.
+__device__ __forceinline__ EqTranspose eq_transpose(const Macro& m, const Parity& pa,
+                                                    AdjointTable K) {
+    const double ux = m.ux, uy = m.uy, T = m.T, a = K->a;
+    const double ux2 = ux * ux, uy2 = uy * uy, u2 = ux2 + uy2, uxy = ux * uy, D = ux2 - uy2;
+    const double E = fma(a, T, u2), A2 = fma(2.0, T, E), A4 = fma(2.0, T, A2);
+    const double xx = ux2 + T, yy = uy2 + T, a2 = a + 2.0, a4 = a + 4.0;
+    double gr, gx, gy, gT;
+    {
+        const double sa = pa.ee[0] + pa.ee[1], da = pa.ee[0] - pa.ee[1];
+        const double sc = pa.ee[3] + pa.ee[4], dc = pa.ee[3] - pa.ee[4];
+        double w[4];   // of 1, E and the sums of the mirrored pairs
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            w[c] = fma(K->eep[0][c], sa,
+                       fma(K->eep[1][c], sc,
+                           fma(K->ees[0][c], pa.ee[2], K->ees[1][c] * pa.ee[5])));
+        const double v2 = fma(K->eep[0][4], da, K->eep[1][4] * dc);   // of their differences
+        const double v4 = fma(K->eep[0][5], da, K->eep[1][5] * dc);
+        // sums: u^2 + 2 T and u^2 A4 + 2 T A2; differences: D and D A4
+        const double s4 = fma(u2, A4, 2.0 * T * A2);
+        gr = fma(w[1], E, w[0]) + fma(w[2], fma(2.0, T, u2), w[3] * s4) + D * fma(v4, A4, v2);
+        const double t = fma(w[3], A4 + u2 + 2.0 * T, w[1] + w[2]);
+        gx = 2.0 * ux * (t + fma(v4, A4 + D, v2));
+        gy = 2.0 * uy * (t - fma(v4, A4 - D, v2));
+        gT = fma(w[1], a, 2.0 * w[2]) + w[3] * fma(u2, a4, 2.0 * fma(T, a2, A2)) + v4 * (D * a4);
+    }
+    {
+        double wo[4], we[4];   // of the moments odd in x and odd in y
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            double so = 0.0, se = 0.0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                so = fma(K->ioe[r][c], pa.oe[r], so);
+                se = fma(K->ioe[r][c < 2 ? c : 5 - c], pa.eo[r], se);
+            }
+            wo[c] = so;
+            we[c] = se;
+        }
+        // moments ux {1, A2, ux^2 + 3T, yy} and uy {1, A2, xx, uy^2 + 3T}
+        const double px = fma(wo[1], A2, wo[0]) + fma(wo[2], fma(3.0, T, ux2), wo[3] * yy);
+        const double py = fma(we[1], A2, we[0]) + fma(we[2], xx, we[3] * fma(3.0, T, uy2));
+        gr += fma(ux, px, uy * py);
+        gx += px + 2.0 * ux * fma(ux, wo[1] + wo[2], uy * (we[1] + we[2]));
+        gy += py + 2.0 * uy * fma(ux, wo[1] + wo[3], uy * (we[1] + we[3]));
+        gT += fma(ux, fma(a2, wo[1], fma(3.0, wo[2], wo[3])),
+                  uy * fma(a2, we[1], fma(3.0, we[3], we[2])));
+    }
+    {
+        const double w0 = fma(K->ioo[0][0], pa.oo[0], K->ioo[1][0] * pa.oo[1]);
+        const double w1 = fma(K->ioo[0][1], pa.oo[0], K->ioo[1][1] * pa.oo[1]);
+        const double p = fma(w1, A4, w0);   // moments uxy {1, A4}
+        gr = fma(uxy, p, gr);
+        gx += uy * fma(2.0 * ux2, w1, p);
+        gy += ux * fma(2.0 * uy2, w1, p);
+        gT = fma(uxy * a4, w1, gT);
+    }
+    // through (rho, u, T) of g: (d q / d g)^T with the factors of rho cancelled
+    EqTranspose t;
+    t.ce = gT * K->inv_a;
+    t.cx = fma(-2.0 * t.ce, ux, gx);
+    t.cy = fma(-2.0 * t.ce, uy, gy);
+    t.c0 = gr - fma(gx, ux, gy * uy) + t.ce * fma(-a, T, u2);
+    return t;
+}
+
+// out = w_add * add + w_in * E'(g)^T a, and per 64 cells of a row the sum of
 // w_in * sum_i a_i dE_i/dtau = w_in * sum_i a_i dt (g_i - g_i^eq) / tau^2
 // written to tau_part (acc = 0) or added to it (acc = 1).
 // The state g is in the storage precision S; adjoint vectors are double.
-// A block is 64 cells of one row (blocks numbered along the row, then row by
-// row) and four waves.  Waves 0 and 1 form the pointwise part: wave 0 the
-// macroscopic state and the tau term, wave 1 the equilibrium transpose,
-// shared through LDS.  Then wave w takes velocities w, w + 4, w + 8 and
-// w + 12 and reads each velocity's stencils, the state on offsets -3 .. 3
-// (for the face selections at -2 .. 2) and the adjoint on -2 .. 2, along x
-// and along y, straight from global memory: neighbouring lanes share cache
-// lines, and a block meets one barrier.  At 97 vector registers five waves
-// fit per SIMD, so a 256^2 grid's 1024 blocks are all resident at once.
-constexpr int ARX = 64, ARW = 4;
-static_assert(NV % ARW == 0, "every wave takes the same number of velocities");
+//
+// A block is 64 cells of one row, one per lane, and two waves that each take
+// the flux transposes of half of the velocities (PART = 0: groups a and b,
+// PART = 1: c and d); of the pointwise part wave 0 forms the equilibrium
+// transpose, handed to the other through LDS, and wave 1 the tau term.
+//
+// The return path of the vector loads bounds it (a 64-bit load of a wave takes
+// 16 cycles of a CU whether it hits or not, and with every stencil offset loaded
+// that path was 86 % busy): the x offsets therefore come from the waves' own
+// centres in LDS, with one load for the columns on either side, and only the y
+// offsets are loaded.  Time of a step's two stages (the four-wave block with
+// both lines loaded / one wave per row, loaded / two waves, loaded / this):
+//   256^2 mixed 31.6 / 29.9 / 22.9 / 21.2 us, FP64 35.0 / 33.4 / 27.3 / 23.5,
+//   1000 x 777 mixed 297 / 207 / 200 / 206, FP64 338 / 254 / 289 / 227,
+//   1800^2 FP64 1474 / 1194 / 1282 / 912.
+// Two rows per block (four waves) cost up to 16 % more on large grids and gain
+// at most 2 % on small ones.  The blocks are numbered in bands (band_index), so
+// that the rows y +- 2 are in the block's own L2: without it 256^2 FP64 25.8,
+// 1800^2 FP64 1060 us.
+struct AdjointArgs {
+    int nx, ny, bc;
+    double w_in, w_add, z, dt_tau2;
+};
 
+// LDS of a block: the x rows of its waves, and what they exchange.
 template <typename S>
-__global__ void __launch_bounds__(ARX * ARW) k_stage_adjoint(const S* __restrict__ g,
-                                                             const double* __restrict__ a,
-                                                             const double* __restrict__ add,
-                                                             double* __restrict__ out,
-                                                             double w_in, double w_add,
-                                                             KParams K,
-                                                             double* __restrict__ tau_part,
-                                                             int acc) {
-    __shared__ double Mq[8][ARX];   // rho, u_x, u_y, T, then q
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int nx = K.nx, ny = K.ny;
-    const int bxn = (nx + ARX - 1) / ARX;
-    const int x = (int)(blockIdx.x % bxn) * ARX + lane, y = (int)(blockIdx.x / bxn);
-    const int64_t cells = (int64_t)nx * ny;
-    const bool inside = x < nx;
-    const int64_t c = (int64_t)y * nx + x;
+struct AdjointRow {
+    S g[2][NX][68];           // six velocities with a component along x each,
+    double a[2][NX][68];      // two halo columns on either side
+    double parity[2][16][64];   // halves of P g, then of P a
+    double eq[4][64];
+};
 
-    // pointwise part, from the parity transforms pg = P g and pa = P a
-    // (P P^T = k I per group, k = 2 axis, 4 diagonal): with h the parity form
-    // of f^eq (f^eq = P^T h), a . (g - f^eq) = pa . (pg / k - h).  Each wave
-    // loads what it needs, so that wave 1 holds pg only until the moments
-    // (this keeps the kernel at 97 registers).
-    double tpart = 0.0;
-    if (w == 0 && inside) {
+template <typename S, int PART>
+__device__ __forceinline__ void stage_adjoint_part(const S* __restrict__ g,
+                                                   const double* __restrict__ a,
+                                                   const double* __restrict__ add,
+                                                   double* __restrict__ out, AdjointTable K, BlockTable I,
+                                                   const AdjointArgs& p, int x0, int y,
+                                                   double* __restrict__ tau_slot, int acc,
+                                                   AdjointRow<S>& sh) {
+    constexpr int NI = NV / 2, I0 = PART * NI, I1 = I0 + NI, K0 = PART * NX;
+    const int nx = p.nx, ny = p.ny, bc = p.bc, lane = threadIdx.x & 63, x = x0 + lane;
+    ColumnLd<S> lg;
+    ColumnLd<double> la;
+    column_offsets<false>(lg, g, x, y, nx, ny, bc);
+    column_offsets<true>(la, a, x, y, nx, ny, bc);
+    S gc[NI];
+    double ac[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        gc[i] = lg(I0 + i, 0);
+        ac[i] = la(I0 + i, 0);
+    }
+    const S hg = halo_value<false, S>(g, K0, x0, y, nx, ny, bc);
+    const double ha = halo_value<true, double>(a, K0, x0, y, nx, ny, bc);
+    AdjointStencil<S> st[3];
+    load_adjoint_stencil(lg, la, I0, st[0]);
+    load_adjoint_stencil(lg, la, I0 + 1, st[1]);
+    __builtin_amdgcn_sched_barrier(0);
+
+    S (&tg)[NX][68] = sh.g[PART];
+    double (&ta)[NX][68] = sh.a[PART];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+        if (SX[I0 + i] != 0) {
+            tg[x_slot(I0 + i) - K0][2 + lane] = gc[i];
+            ta[x_slot(I0 + i) - K0][2 + lane] = ac[i];
+        }
+    if (lane < 4 * NX) {
+        const int h = lane & 3, c = h < 2 ? h : 64 + h;
+        tg[lane >> 2][c] = hg;
+        ta[lane >> 2][c] = ha;
+    }
+    EqTranspose eq;
+    {
         Parity pg, pa;
-        {
-            double v[NV];
+        double v[8], c[8];
 #pragma unroll
-            for (int i = 0; i < NV; ++i) v[i] = (double)g[i * cells + c];
-            to_parity(v, pg);
+        for (int i = 0; i < 8; ++i) v[i] = (double)gc[i];
+        half_parity(v, c);
+        set_half(pg, PART, c);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sh.parity[PART][i][lane] = c[i];
+        half_parity(ac, c);
+        set_half(pa, PART, c);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sh.parity[PART][8 + i][lane] = c[i];
+        __syncthreads();   // also orders the x rows, which a wave reads only of its own
+#pragma unroll
+        for (int i = 0; i < 8; ++i) c[i] = sh.parity[1 - PART][i][lane];
+        set_half(pg, 1 - PART, c);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) c[i] = sh.parity[1 - PART][8 + i][lane];
+        set_half(pa, 1 - PART, c);
+        const double rho = ((pg.ee[0] + pg.ee[1]) + (pg.ee[2] + pg.ee[3])) + (pg.ee[4] + pg.ee[5]);
+        double jx = 0.0, jy = 0.0, e2 = 0.0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            jx = fma(K->jv[c], pg.oe[c], jx);
+            jy = fma(K->jv[c], pg.eo[c], jy);
         }
-        {
-            double v[NV];
+        constexpr int group[6] = {0, 0, 1, 2, 2, 3};
 #pragma unroll
-            for (int i = 0; i < NV; ++i) v[i] = a[i * cells + c];
-            to_parity(v, pa);
+        for (int c = 0; c < 6; ++c) e2 = fma(K->en[group[c]], pg.ee[c], e2);
+        const Macro m = macro_of(rho, jx, jy, e2, K->inv_a);
+        if constexpr (PART == 0) {
+            eq = eq_transpose(m, pa, K);
+            sh.eq[0][lane] = eq.c0;
+            sh.eq[1][lane] = eq.cx;
+            sh.eq[2][lane] = eq.cy;
+            sh.eq[3][lane] = eq.ce;
+        } else {
+            // a . (g - f^eq) = pa . (pg / k - h), P P^T = k I per group (2 for the
+            // axis pairs, 4 for the rest)
+            Parity h;
+            equilibrium_parity(m, *I, I->a, h);
+            double d = 0.0;
+#pragma unroll
+            for (int r = 0; r < 6; ++r)
+                d = fma(pa.ee[r], fma((r == 2 || r == 5) ? 0.25 : 0.5, pg.ee[r], -h.ee[r]), d);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double k = (r & 1) ? 0.25 : 0.5;
+                d = fma(pa.oe[r], fma(k, pg.oe[r], -h.oe[r]), d);
+                d = fma(pa.eo[r], fma(k, pg.eo[r], -h.eo[r]), d);
+            }
+#pragma unroll
+            for (int r = 0; r < 2; ++r) d = fma(pa.oo[r], fma(0.25, pg.oo[r], -h.oo[r]), d);
+            // the partial of the 64 cells, summed in a fixed order
+            double v = x < nx ? p.dt_tau2 * d * p.w_in : 0.0;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+            if (lane == 0) *tau_slot = acc ? *tau_slot + v : v;
         }
-        const Macro m = macro_from_parity(pg, K, K.inv_a);
-        Parity h;
-        equilibrium_parity(m, K, K.a, h);
-        double d = 0.0;
-#pragma unroll
-        for (int r = 0; r < 6; ++r)
-            d = fma(pa.ee[r], fma((r == 2 || r == 5) ? 0.25 : 0.5, pg.ee[r], -h.ee[r]), d);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const double k = (r & 1) ? 0.25 : 0.5;
-            d = fma(pa.oe[r], fma(k, pg.oe[r], -h.oe[r]), d);
-            d = fma(pa.eo[r], fma(k, pg.eo[r], -h.eo[r]), d);
-        }
-#pragma unroll
-        for (int r = 0; r < 2; ++r) d = fma(pa.oo[r], fma(0.25, pg.oo[r], -h.oo[r]), d);
-        tpart = (K.dt / (K.tau * K.tau)) * d;
-        Mq[0][lane] = m.rho;
-        Mq[1][lane] = m.ux;
-        Mq[2][lane] = m.uy;
-        Mq[3][lane] = m.T;
-    } else if (w == 1 && inside) {
-        Macro m;
-        {
-            Parity pg;
-            double v[NV];
-#pragma unroll
-            for (int i = 0; i < NV; ++i) v[i] = (double)g[i * cells + c];
-            to_parity(v, pg);
-            m = macro_from_parity(pg, K, K.inv_a);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        Parity pa;
-        {
-            double v[NV];
-#pragma unroll
-            for (int i = 0; i < NV; ++i) v[i] = a[i * cells + c];
-            to_parity(v, pa);
-        }
-        const Quad q = equilibrium_vjp_q_parity(m, K, K.a, pa);
-        Mq[4][lane] = q.rho;
-        Mq[5][lane] = q.ux;
-        Mq[6][lane] = q.uy;
-        Mq[7][lane] = q.T;
     }
     __syncthreads();
-    if (w == 0) {   // the block's tau partial, summed in a fixed order
-        double v = tpart * w_in;
+    if constexpr (PART == 1)
+        eq = EqTranspose{sh.eq[0][lane], sh.eq[1][lane], sh.eq[2][lane], sh.eq[3][lane]};
+    // 0 where a face of the cell is the edge of a zero-gradient side
+    const double kxm = (bc & 1) && x == 0 ? 0.0 : 1.0, kxp = (bc & 1) && x == nx - 1 ? 0.0 : 1.0;
+    const double kym = (bc & 2) && y == 0 ? 0.0 : 1.0, kyp = (bc & 2) && y == ny - 1 ? 0.0 : 1.0;
+    const double w1 = p.w_in * (1.0 - p.z), w2 = p.w_in * p.z;
+    double cx[2], cy[2], vg[2], base[2];
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if (lane == 0) tau_part[blockIdx.x] = acc ? tau_part[blockIdx.x] + v : v;
+    for (int k = 0; k < 2; ++k) {
+        const int gr = 2 * PART + k;
+        cx[k] = K->cd[0][gr];
+        cy[k] = K->cd[0][4 + gr];
+        vg[k] = K->jv[gr];
+        base[k] = fma(eq.ce, K->en[gr], eq.c0);
     }
-    if (!inside) return;
-    const Macro m{Mq[0][lane], Mq[1][lane], Mq[2][lane], Mq[3][lane]};
-    const Quad q{Mq[4][lane], Mq[5][lane], Mq[6][lane], Mq[7][lane]};
-
-    // stencil positions, offsets -3 .. 3, through the boundary conditions;
-    // the adjoint is zero at zero-gradient ghosts
-    const int64_t row = (int64_t)y * nx;
-    int xs[7], ys[7];
-    bool xg[7], yg[7];
+    const bool inside = x < nx;
+    const int64_t at = (int64_t)y * nx + min(x, nx - 1), cells = (int64_t)nx * ny;
 #pragma unroll
-    for (int d = -3; d <= 3; ++d) {
-        xs[d + 3] = wrap_or_clamp(x + d, nx, K.bcx);
-        ys[d + 3] = wrap_or_clamp(y + d, ny, K.bcy);
-        xg[d + 3] = K.bcx != CDBM_PERIODIC && (x + d < 0 || x + d >= nx);
-        yg[d + 3] = K.bcy != CDBM_PERIODIC && (y + d < 0 || y + d >= ny);
-    }
-#pragma unroll 1
-    for (int j = 0; j < NV / ARW; ++j) {
-        const int i = w + ARW * j;
-        const int sx = SX[i], sy = SY[i];
-        const S* gi = g + i * cells;
-        const double* ai = a + i * cells;
-        const S fc = gi[c];
-        const double ac = ai[c];
+    for (int i = I0; i < I1; ++i) {
+        if (i + 2 < I1) load_adjoint_stencil(lg, la, i + 2, st[(i + 2 - I0) % 3]);
+        double prior = 0.0;
+        if (p.w_add != 0.0) prior = add[i * cells + at];
+        __builtin_amdgcn_sched_barrier(0);
+        const int k = (i - I0) / 4;
+        const double aci = ac[i - I0];
         double adv = 0.0;
-        if (sx != 0) {
-            S F[7];
-            RegSel Sl;
-            RegLine A;
+        if (SX[i] != 0) {
+            S f[5];
+            double A[5];
 #pragma unroll
-            for (int d = 0; d < 7; ++d) F[d] = d == 3 ? fc : gi[row + xs[d]];
-#pragma unroll
-            for (int d = 0; d < 5; ++d) {
-                Sl.c[d] = face_code<S>(F[d], F[d + 1], F[d + 2]);
-                A.v[d] = d == 2 ? ac : (xg[d + 1] ? 0.0 : ai[row + xs[d + 1]]);
+            for (int o = -2; o <= 2; ++o) {
+                const bool need = o != (SX[i] > 0 ? -2 : 2);
+                f[o + 2] = o == 0 ? gc[i - I0] : tg[x_slot(i) - K0][2 + lane + o];
+                A[o + 2] = o == 0 ? aci : (need ? ta[x_slot(i) - K0][2 + lane + o] : 0.0);
             }
-            if (sx > 0)
-                adv += K.cx[i] * nnd_transpose<true>(Sl, A, 0, x, nx, K.bcx);
-            else
-                adv += K.cx[i] * nnd_transpose<false>(Sl, A, 0, x, nx, K.bcx);
+            if (SX[i] > 0) adv = cx[k] * nnd_transpose<true, S>(f, A, kxm, kxp);
+            else adv = -cx[k] * nnd_transpose<false, S>(f, A, kxm, kxp);
         }
-        if (sy != 0) {
-            S F[7];
-            RegSel Sl;
-            RegLine A;
-#pragma unroll
-            for (int d = 0; d < 7; ++d) F[d] = d == 3 ? fc : gi[(int64_t)ys[d] * nx + x];
-#pragma unroll
-            for (int d = 0; d < 5; ++d) {
-                Sl.c[d] = face_code<S>(F[d], F[d + 1], F[d + 2]);
-                A.v[d] = d == 2 ? ac : (yg[d + 1] ? 0.0 : ai[(int64_t)ys[d + 1] * nx + x]);
-            }
-            if (sy > 0)
-                adv += K.cy[i] * nnd_transpose<true>(Sl, A, 0, y, ny, K.bcy);
-            else
-                adv += K.cy[i] * nnd_transpose<false>(Sl, A, 0, y, ny, K.bcy);
-        }
-        const double ceq = moments_vjp_k(m, K, K.a, q, i);
-        double v = ac + adv - K.z * (ac - ceq);
-        v *= w_in;
-        if (w_add != 0.0) v = fma(w_add, add[i * cells + c], v);
-        out[i * cells + c] = v;
+        AdjointStencil<S>& s = st[(i - I0) % 3];
+        s.f[2] = gc[i - I0];
+        s.a[2] = aci;
+        if (SY[i] > 0) adv = fma(cy[k], nnd_transpose<true, S>(s.f, s.a, kym, kyp), adv);
+        else if (SY[i] < 0) adv = fma(-cy[k], nnd_transpose<false, S>(s.f, s.a, kym, kyp), adv);
+        double ceq = base[k];
+        if (SX[i] != 0) ceq = fma(SX[i] > 0 ? vg[k] : -vg[k], eq.cx, ceq);
+        if (SY[i] != 0) ceq = fma(SY[i] > 0 ? vg[k] : -vg[k], eq.cy, ceq);
+        double r = fma(p.w_in, adv, fma(w1, aci, w2 * ceq));
+        r = fma(p.w_add, prior, r);
+        if (inside) out[i * cells + at] = r;
+        __builtin_amdgcn_sched_barrier(0);
     }
+}
+
+template <typename S>
+__global__ void __launch_bounds__(128) k_stage_adjoint(
+    const S* __restrict__ g, const double* __restrict__ a, const double* __restrict__ add,
+    double* __restrict__ out, const StageParams* __restrict__ Kd, const KParams* __restrict__ Bd,
+    AdjointArgs p,
+    double* __restrict__ tau_part, int acc) {
+    __shared__ AdjointRow<S> row;
+    const uint32_t per_row = (uint32_t)(p.nx + 63) / 64;
+    const uint32_t b = band_index(blockIdx.x, gridDim.x);
+    const int y = (int)(b / per_row), x0 = (int)(b - (uint32_t)y * per_row) * 64;
+    const AdjointTable K = (AdjointTable)(uintptr_t)Kd;
+    const BlockTable I = (BlockTable)(uintptr_t)Bd;
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0)
+        stage_adjoint_part<S, 0>(g, a, add, out, K, I, p, x0, y, tau_part + b, acc, row);
+    else
+        stage_adjoint_part<S, 1>(g, a, add, out, K, I, p, x0, y, tau_part + b, acc, row);
 }
 
 // Sum of part[i], part[i + step], ... (i < n) over the 1024 threads of a
@@ -286,16 +520,18 @@ inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1)
 }  // namespace
 
 int stage_adjoint_blocks(const KParams& K) {
-    return (int)(blocks_for(K.nx, ARX) * (unsigned)K.ny);
+    return (int)(blocks_for(K.nx, 64) * (unsigned)K.ny);
 }
 
 template <typename S>
 hipError_t launch_stage_adjoint(const void* g, const void* a, const void* add, void* out,
                                 double* tau_part, bool tau_add, double w_in, double w_add,
-                                const KParams& K, hipStream_t st) {
-    hipLaunchKernelGGL(k_stage_adjoint<S>, dim3(stage_adjoint_blocks(K)), dim3(ARX * ARW), 0, st,
-                       (const S*)g, (const double*)a, (const double*)add, (double*)out, w_in,
-                       w_add, K, tau_part, tau_add ? 1 : 0);
+                                const KParams& K, const StageParams* Kd, const KParams* Bd,
+                                hipStream_t st) {
+    const AdjointArgs p{K.nx, K.ny, K.bcx | K.bcy << 1, w_in, w_add, K.z, K.dt / (K.tau * K.tau)};
+    hipLaunchKernelGGL(k_stage_adjoint<S>, dim3(stage_adjoint_blocks(K)), dim3(128), 0, st,
+                       (const S*)g, (const double*)a, (const double*)add, (double*)out, Kd, Bd, p,
+                       tau_part, tau_add ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -336,7 +572,7 @@ hipError_t launch_accumulate_scalar(double* part, int n, double* scratch, double
 #define CDBM_INSTANTIATE(S)                                                                      \
     template hipError_t launch_stage_adjoint<S>(const void*, const void*, const void*, void*,   \
                                                 double*, bool, double, double, const KParams&,  \
-                                                hipStream_t);                                   \
+                                                const StageParams*, const KParams*, hipStream_t); \
     template hipError_t launch_init_adjoint<S>(const double*, const double*, const double*,     \
                                                const double*, const void*, double*, double*,    \
                                                double*, double*, const KParams&, hipStream_t);  \

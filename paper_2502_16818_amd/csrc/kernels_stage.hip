@@ -36,15 +36,6 @@ struct StageLd {
     }
 };
 
-// wrap_or_clamp for an index at most 2 off the grid.
-__device__ __forceinline__ int wrap_by_two(int i, int n, bool periodic) {
-    if (periodic) {
-        if (n == 1) return 0;
-        return i < 0 ? i + n : (i >= n ? i - n : i);
-    }
-    return min(max(i, 0), n - 1);
-}
-
 // The stencil of a velocity without its centre, upwind first: s[0..2] along x,
 // s[3..5] along y.
 template <typename S>

@@ -69,14 +69,15 @@ template <typename S>
 hipError_t launch_line_steps(const void* fin, void* fout, int steps, const KParams& K,
                              const QuadParams* Qd, hipStream_t st);
 
-// Adjoint (kernels_adjoint.hip).  tau_part: one double per block
-// (stage_adjoint_blocks), the block sums of the launch's tau term, written
-// or (tau_add) added to what it holds.
+// Adjoint (kernels_adjoint.hip).  tau_part: one double per 64 cells of a row
+// (stage_adjoint_blocks), the sums of the launch's tau term, written or
+// (tau_add) added to what it holds.
 int stage_adjoint_blocks(const KParams& K);
 template <typename S>
 hipError_t launch_stage_adjoint(const void* f, const void* lam, const void* lam_add, void* out,
                                 double* tau_part, bool tau_add, double w_in, double w_add,
-                                const KParams& K, hipStream_t st);
+                                const KParams& K, const StageParams* Kd, const KParams* Bd,
+                                hipStream_t st);
 template <typename S>
 hipError_t launch_init_adjoint(const double* rho, const double* ux, const double* uy,
                                const double* T, const void* lam, double* g_rho, double* g_ux,
