@@ -189,11 +189,12 @@ namespace {
 
 // With CDBM_STEP_AUTO, grids of up to this many cells take the step as two
 // single-stage launches (f^(1) through the handle's stage buffer): one cell
-// per thread fills the chip, where the fused step has too few rows per block
-// to hide its per-iteration latency (measured crossovers: about 700 x 700
-// cells in the mixed form, about 560 x 560 in FP64).
-constexpr int64_t SPLIT_STEP_CELLS_MIXED = int64_t(1) << 19;   // 724 x 724
-constexpr int64_t SPLIT_STEP_CELLS_FP64 = int64_t(1) << 18;    // 512 x 512
+// per lane fills the chip, where the fused step has too few rows per block
+// to hide its per-iteration latency.  Single stages / fused: mixed 512^2 18.4 /
+// 39.9 us, 724^2 36.2 / 40.5, 800^2 40.7 / 40.8, 900^2 52.4 / 44.9; FP64 512^2
+// 34.7 / 44.6, 600^2 45.4 / 45.0, 660^2 54.5 / 45.7.
+constexpr int64_t SPLIT_STEP_CELLS_MIXED = 600000;
+constexpr int64_t SPLIT_STEP_CELLS_FP64 = 350000;
 
 hipError_t step_once(const cdbm_handle* h, const void* fin, void* fout, hipStream_t st) {
     if (h->tile)

@@ -166,9 +166,9 @@ __device__ __forceinline__ void equilibrium(const Macro& m, const KParams& K, do
 // the parity combinations of k (f - f^eq) are g_r - k rho (B m-hat)_r, and
 // unpacking them (additions only) gives k (f_i - f_i^eq).
 // Table: const KParams or const StageParams (in any address space).
-template <class Table>
+template <int Q0 = 0, int Q1 = 2, class Table>
 __device__ __forceinline__ void nonequilibrium(const Parity& g, const Macro& m, Table& K,
-                                               double a, double out[NV], int z = 0) {
+                                               double a, double* out, int z = 0) {
     const double ux = m.ux, uy = m.uy, T = m.T;
     const double ux2 = ux * ux, uy2 = uy * uy, u2 = fma(ux, ux, uy2), uxy = ux * uy;
     const double E = fma(a, T, u2);        // u^2 + (D+I) T
@@ -189,7 +189,7 @@ __device__ __forceinline__ void nonequilibrium(const Parity& g, const Macro& m, 
     const double s23 = mee[2] + mee[3], d23 = mee[2] - mee[3];
     const double s45 = mee[4] + mee[5], d45 = mee[4] - mee[5];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
+    for (int q = Q0; q < Q1; ++q) {
         const int r0 = 3 * q;   // pair (r0, r0 + 1), axis groups: n2
         const double P =
             fma(K.eep[q][3 + z], s45, fma(K.eep[q][2 + z], s23, K.eep[q][1 + z] * mee[1]));
@@ -202,7 +202,7 @@ __device__ __forceinline__ void nonequilibrium(const Parity& g, const Macro& m, 
         tee[rd] = fma(n4, D, fma(n4, K.ees[q][z], g.ee[rd]));
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 2 * Q0; r < 2 * Q1; ++r) {
         double so = 0.0, se = 0.0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -214,11 +214,11 @@ __device__ __forceinline__ void nonequilibrium(const Parity& g, const Macro& m, 
         teo[r] = fma(n, se, g.eo[r]);
     }
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+    for (int r = Q0; r < Q1; ++r)
         too[r] = fma(n4, fma(K.ioo[r][z], moo[0], K.ioo[r][1 + z] * moo[1]), g.oo[r]);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int a0 = 8 * q, d0 = 8 * q + 4;
+    for (int q = Q0; q < Q1; ++q) {
+        const int a0 = 8 * (q - Q0), d0 = a0 + 4;
         out[a0 + 0] = tee[3 * q + 0] + toe[2 * q];
         out[a0 + 2] = tee[3 * q + 0] - toe[2 * q];
         out[a0 + 1] = tee[3 * q + 1] + teo[2 * q];
@@ -247,23 +247,6 @@ __device__ __forceinline__ int wrap_or_clamp(int i, int n, int bc) {
         return i < 0 ? i + n : i;
     }
     return i < 0 ? 0 : (i >= n ? n - 1 : i);
-}
-
-// Position of block b of n in a numbering whose consecutive blocks run on one
-// XCD: the hardware hands blocks to the eight XCDs in turn, each with an L2 of
-// its own, so blocks that share rows have to be eight apart to share a cache.
-__device__ __forceinline__ uint32_t band_index(uint32_t b, uint32_t n) {
-    const uint32_t per = n / 8;
-    return b < 8 * per ? (b % 8) * per + b / 8 : b;
-}
-
-// wrap_or_clamp for an index at most 2 off the grid.
-__device__ __forceinline__ int wrap_by_two(int i, int n, bool periodic) {
-    if (periodic) {
-        if (n == 1) return 0;
-        return i < 0 ? i + n : (i >= n ? i - n : i);
-    }
-    return min(max(i, 0), n - 1);
 }
 
 }  // namespace cdbm

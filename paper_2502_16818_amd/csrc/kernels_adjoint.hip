@@ -4,6 +4,7 @@
 
 #include "adjoint.hpp"
 #include "launch.hpp"
+#include "row_block.hpp"
 
 namespace cdbm {
 
@@ -43,7 +44,7 @@ __device__ __forceinline__ void column_offsets(ColumnLd<T>& ld, const void* f, i
     ld.p = (const char*)f;
     ld.plane = (int64_t)nx * ny * (int64_t)sizeof(T);
     const bool px = !(bc & 1), py = !(bc & 2);
-    const int cx = x < nx ? x : wrap_or_clamp(x, nx, bc & 1);
+    const int cx = block_column(x, nx, px);
     const bool gx = GHOSTS_ZERO && !px && x >= nx;
 #pragma unroll
     for (int o = -2; o <= 2; ++o) {
@@ -52,30 +53,6 @@ __device__ __forceinline__ void column_offsets(ColumnLd<T>& ld, const void* f, i
         ld.row[o + 2] = (uint32_t)cy * (uint32_t)nx * (uint32_t)sizeof(T);
         ld.col[o + 2] = gx || gy ? OUTSIDE : (uint32_t)cx * (uint32_t)sizeof(T);
     }
-}
-
-// Velocities of a part with a component along x, in order, and the position of
-// velocity i among them (three of every four: the axis groups have two, the
-// diagonal ones four).
-constexpr int x_slot(int i) { return (i / 8) * 6 + ((i / 4) % 2 == 0 ? (i % 4) / 2 : 2 + i % 4); }
-constexpr int x_velocity(int k) { return (k / 6) * 8 + (k % 6 < 2 ? 2 * (k % 6) : 2 + k % 6); }
-static_assert(x_slot(0) == 0 && x_slot(2) == 1 && x_slot(4) == 2 && x_slot(15) == 11 &&
-                  x_velocity(1) == 2 && x_velocity(2) == 4 && x_velocity(11) == 15,
-              "velocities 0, 2, 4 .. 7, 8, 10, 12 .. 15");
-
-// The two columns on either side of a wave's 64 columns, for the x differences
-// of all its velocities in one load: lane 4 k + h takes column h (-2, -1, 64,
-// 65) of the k-th velocity with a component along x.
-constexpr int NX = 6;   // those of a part
-template <bool GHOSTS_ZERO, typename T>
-__device__ __forceinline__ T halo_value(const void* f, int k0, int x0, int y, int nx, int ny,
-                                        int bc) {
-    const int lane = threadIdx.x & 63, h = lane & 3;
-    const int k = min(lane >> 2, NX - 1);
-    const int x = x0 + (h < 2 ? h - 2 : 62 + h), cx = wrap_or_clamp(x, nx, bc & 1);
-    const int i = x_velocity(k0 + k);
-    const T v = ((const T*)f)[((int64_t)i * ny + y) * nx + cx];
-    return GHOSTS_ZERO && (bc & 1) && cx != x ? T(0) : v;
 }
 
 // One velocity's y stencils without the centres: the state at offsets -2 .. 2
@@ -101,30 +78,6 @@ __device__ __forceinline__ void load_adjoint_stencil(ColumnLd<S> g, ColumnLd<dou
         // v > 0 reads the adjoint at -1, 1, 2 and v < 0 at -2, -1, 1
         s.a[o + 2] = (o != (SY[i] > 0 ? -2 : 2)) ? a(i, o) : 0.0;
     }
-}
-
-// Parity combinations of groups 2 q and 2 q + 1 (v: their eight values).
-__device__ __forceinline__ void half_parity(const double v[8], double c[8]) {
-    c[0] = v[0] + v[2];
-    c[1] = v[1] + v[3];
-    c[2] = v[0] - v[2];
-    c[3] = v[1] - v[3];
-    const double s01 = v[4] + v[5], s23 = v[6] + v[7];
-    const double d01 = v[4] - v[5], d23 = v[6] - v[7];
-    c[4] = s01 + s23;
-    c[5] = d01 - d23;
-    c[6] = s01 - s23;
-    c[7] = d01 + d23;
-}
-__device__ __forceinline__ void set_half(Parity& g, int q, const double c[8]) {
-    g.ee[3 * q] = c[0];
-    g.ee[3 * q + 1] = c[1];
-    g.ee[3 * q + 2] = c[4];
-    g.oe[2 * q] = c[2];
-    g.oe[2 * q + 1] = c[5];
-    g.eo[2 * q] = c[3];
-    g.eo[2 * q + 1] = c[6];
-    g.oo[q] = c[7];
 }
 
 // The equilibrium transpose of a cell as a polynomial in the velocity:
@@ -233,8 +186,8 @@ struct AdjointArgs {
 // LDS of a block: the x rows of its waves, and what they exchange.
 template <typename S>
 struct AdjointRow {
-    S g[2][NX][68];           // six velocities with a component along x each,
-    double a[2][NX][68];      // two halo columns on either side
+    S g[2][NVX / 2][68];           // six velocities with a component along x each,
+    double a[2][NVX / 2][68];      // two halo columns on either side
     double parity[2][16][64];   // halves of P g, then of P a
     double eq[4][64];
 };
@@ -247,7 +200,7 @@ __device__ __forceinline__ void stage_adjoint_part(const S* __restrict__ g,
                                                    const AdjointArgs& p, int x0, int y,
                                                    double* __restrict__ tau_slot, int acc,
                                                    AdjointRow<S>& sh) {
-    constexpr int NI = NV / 2, I0 = PART * NI, I1 = I0 + NI, K0 = PART * NX;
+    constexpr int NI = NV / 2, I0 = PART * NI, I1 = I0 + NI, NX = NVX / 2, K0 = PART * NX;
     const int nx = p.nx, ny = p.ny, bc = p.bc, lane = threadIdx.x & 63, x = x0 + lane;
     ColumnLd<S> lg;
     ColumnLd<double> la;
@@ -260,8 +213,8 @@ __device__ __forceinline__ void stage_adjoint_part(const S* __restrict__ g,
         gc[i] = lg(I0 + i, 0);
         ac[i] = la(I0 + i, 0);
     }
-    const S hg = halo_value<false, S>(g, K0, x0, y, nx, ny, bc);
-    const double ha = halo_value<true, double>(a, K0, x0, y, nx, ny, bc);
+    const S hg = halo_value<S>(g, K0, NX, x0, y, nx, ny, !(bc & 1), false);
+    const double ha = halo_value<double>(a, K0, NX, x0, y, nx, ny, !(bc & 1), true);
     AdjointStencil<S> st[3];
     load_adjoint_stencil(lg, la, I0, st[0]);
     load_adjoint_stencil(lg, la, I0 + 1, st[1]);
@@ -276,7 +229,7 @@ __device__ __forceinline__ void stage_adjoint_part(const S* __restrict__ g,
             ta[x_slot(I0 + i) - K0][2 + lane] = ac[i];
         }
     if (lane < 4 * NX) {
-        const int h = lane & 3, c = h < 2 ? h : 64 + h;
+        const int c = halo_place();
         tg[lane >> 2][c] = hg;
         ta[lane >> 2][c] = ha;
     }

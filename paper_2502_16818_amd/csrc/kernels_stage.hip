@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include "launch.hpp"
+#include "row_block.hpp"
 #include "step_fused.hpp"
 
 namespace cdbm {
@@ -11,21 +12,19 @@ namespace {
 
 typedef const __attribute__((address_space(4))) StageParams* StageTable;
 
-// Neighbour reads of one cell.  A wave is 64 cells of one row, so the rows'
-// offsets are scalar and only the five columns are vector operands: a load
-// takes one scalar addition for its plane and nothing on the vector unit
-// (with 64-bit addresses and the wrap's divisions these were a third of the
-// stage's vector instructions).
+// Reads of a block's planes at the lane's column.  A block is 64 cells of one
+// row, so the rows' offsets are scalar and only the column is a vector operand:
+// a load takes one scalar addition for its plane and nothing on the vector unit.
 template <typename S>
 struct StageLd {
     const char* f;
     int64_t plane;       // bytes of a plane (at most 2^31)
     uint32_t row[5];     // byte offsets in a plane of the rows at offset -2 .. 2
-    uint32_t col[5];     // byte offsets in a row of the columns at offset -2 .. 2
-    __device__ __forceinline__ S operator()(int i, int ox, int oy) const {
+    uint32_t col;        // byte offset in a row of the lane's column
+    __device__ __forceinline__ S operator()(int i, int oy) const {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char*>(f) + i * plane, 0, (int)(uint32_t)plane, 0x00020000);
-        const int v = (int)col[ox + 2], s = (int)row[oy + 2];
+        const int v = (int)col, s = (int)row[oy + 2];
         if constexpr (sizeof(S) == 4) {
             return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, v, s, 0));
         } else {
@@ -36,19 +35,23 @@ struct StageLd {
     }
 };
 
-// The stencil of a velocity without its centre, upwind first: s[0..2] along x,
-// s[3..5] along y.
+// The stencil of a velocity without its centre, upwind first: s[0..2] along x
+// (from r, the block's row of this velocity, the cell at r[2 + lane]), s[3..5]
+// along y.
 template <typename S>
-__device__ __forceinline__ void load_stencil(const StageLd<S>& ld, int i, S s[6]) {
-    if (SX[i] > 0) {
-        s[0] = ld(i, -2, 0); s[1] = ld(i, -1, 0); s[2] = ld(i, 1, 0);
-    } else if (SX[i] < 0) {
-        s[0] = ld(i, -1, 0); s[1] = ld(i, 1, 0); s[2] = ld(i, 2, 0);
-    }
+__device__ __forceinline__ void load_stencil_y(const StageLd<S>& ld, int i, S s[6]) {
     if (SY[i] > 0) {
-        s[3] = ld(i, 0, -2); s[4] = ld(i, 0, -1); s[5] = ld(i, 0, 1);
+        s[3] = ld(i, -2); s[4] = ld(i, -1); s[5] = ld(i, 1);
     } else if (SY[i] < 0) {
-        s[3] = ld(i, 0, -1); s[4] = ld(i, 0, 1); s[5] = ld(i, 0, 2);
+        s[3] = ld(i, -1); s[4] = ld(i, 1); s[5] = ld(i, 2);
+    }
+}
+template <typename S>
+__device__ __forceinline__ void read_stencil_x(const S* r, int lane, int i, S s[6]) {
+    if (SX[i] > 0) {
+        s[0] = r[lane]; s[1] = r[lane + 1]; s[2] = r[lane + 3];
+    } else if (SX[i] < 0) {
+        s[0] = r[lane + 1]; s[1] = r[lane + 3]; s[2] = r[lane + 4];
     }
 }
 
@@ -99,54 +102,82 @@ __device__ __forceinline__ void stage_conserved(const Parity& g, StageTable K, d
 // in double (two floats of like size), so the advection terms of
 // neighbouring cells cancel in the grid sums to FP64 rounding.
 //
-// The stencils of groups a and b are requested together with the cell's own
-// values, so that they arrive during the moment arithmetic, and those of c
-// and d (and the Heun terms) right after it; left to itself the compiler
-// fetched values where it needed them, a wait each.  Bound by latencies up to
-// about 384 x 384 and by the cache traffic of the stencils above; against 64-bit
-// addresses and wraps by division (926 vector instructions in the mixed first
-// stage, now 515): 256 x 256 mixed 6.9 -> 5.7 us, 512 x 512 compensated
-// 17.4 -> 15.9 us, FP64 21.9 -> 19.3 us a stage.
-template <typename S, bool STAGE2, bool COMP>
-__global__ void __launch_bounds__(256) k_stage(const S* __restrict__ fin,
-                                               const S* __restrict__ base, S* __restrict__ fout,
-                                               const StageParams* __restrict__ Kd, int nx, int ny,
-                                               int bc) {
-    using A = typename std::conditional<COMP, double, S>::type;
+// A block is 64 cells of a row and PARTS waves, each with the fluxes of 16 / PARTS
+// velocities; two waves exchange the parity halves of their values through LDS
+// and each form the moments.  The y stencils are requested together with the
+// cell's own values (of one wave: those of half of its velocities, the rest and
+// the Heun terms right after the moment arithmetic), so that they arrive during
+// that arithmetic.  Bound by latencies up to about 384 x 384, above by the return
+// path of the vector loads (8 cycles of a CU for a 32-bit load of a wave, 16 for
+// a 64-bit one) and by the FP64 arithmetic.  With x offsets loaded too, blocks of
+// four rows and blocks in the grid's own order, a step of two stages took:
+//   256^2 mixed 13.2 -> 8.8 us, FP64 17.7 -> 12.1, compensated 14.3 -> 11.7,
+//   512^2 mixed 24.3 -> 18.4, FP64 38.7 -> 34.8, compensated 31.7 -> 28.7,
+//   724^2 mixed 48.6 -> 35.6, FP64 79.1 -> 63.3, compensated 63.8 -> 51.9
+// (one row per block 512^2 mixed 22.1 against four 22.9, eight 24.7; the band
+// order of blocks: 256^2 mixed 13.2 -> 10.6, FP64 17.7 -> 13.6).
+// LDS of a block of PARTS waves: their x rows and the parity halves they exchange.
+template <typename S, bool COMP, int PARTS>
+struct StageRow {
+    S x[PARTS][NVX / PARTS][68];
+    double half[PARTS > 1 ? 1 + COMP : 1][PARTS][PARTS > 1 ? 8 : 1][64];
+};
+
+template <int PART, int PARTS, typename Row>
+__device__ __forceinline__ void exchange_half(Row& half, const double v[8], Parity& g) {
     const int lane = threadIdx.x & 63;
-    const int x = blockIdx.x * 64 + lane;
-    const int y = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (y >= ny) return;
+    double c[8];
+    half_parity(v, c);
+    set_half(g, PART, c);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) half[PART][i][lane] = c[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) c[i] = half[1 - PART][i][lane];
+    set_half(g, 1 - PART, c);
+}
+
+template <typename S, bool STAGE2, bool COMP, int PART, int PARTS>
+__device__ __forceinline__ void stage_part(const S* __restrict__ fin, const S* __restrict__ base,
+                                           S* __restrict__ fout, StageTable K, int nx, int ny,
+                                           int bc, int x0, int y, StageRow<S, COMP, PARTS>& sh) {
+    using A = typename std::conditional<COMP, double, S>::type;
+    constexpr int NI = NV / PARTS, I0 = PART * NI, NX = NVX / PARTS, K0 = PART * NX;
+    const int lane = threadIdx.x & 63, x = x0 + lane;
+    const bool px = !(bc & 1), py = !(bc & 2);
     StageLd<S> ld;
     ld.f = (const char*)fin;
     ld.plane = (int64_t)nx * ny * (int64_t)sizeof(S);
     const uint32_t pitch = (uint32_t)nx * (uint32_t)sizeof(S);
+    ld.col = (uint32_t)block_column(x, nx, px) * (uint32_t)sizeof(S);
 #pragma unroll
-    for (int o = -2; o <= 2; ++o) {
-        ld.col[o + 2] = (uint32_t)wrap_by_two(min(x, nx - 1) + o, nx, !(bc & 1)) * (uint32_t)sizeof(S);
-        ld.row[o + 2] = (uint32_t)wrap_by_two(y + o, ny, !(bc & 2)) * pitch;
-    }
+    for (int o = -2; o <= 2; ++o) ld.row[o + 2] = (uint32_t)wrap_by_two(y + o, ny, py) * pitch;
     StageLd<S> lb = ld;
     lb.f = (const char*)base;
-    S f[NV], st[NV][6], rf[4], hb[NV];
+    S f[NI], st[NI][6], rf[4], hb[NI];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) f[i] = ld(i, 0, 0);
+    for (int i = 0; i < NI; ++i) f[i] = ld(I0 + i, 0);
     if constexpr (COMP) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) rf[k] = ld(NV + k, 0, 0);
+        for (int k = 0; k < 4; ++k) rf[k] = ld(NV + k, 0);
     }
+    const S halo = halo_value<S>(fin, K0, NX, x0, y, nx, ny, px, false);
 #pragma unroll
-    for (int i = 0; i < NV / 2; ++i) load_stencil(ld, i, st[i]);
-    const StageTable K = (StageTable)(uintptr_t)Kd;
+    for (int i = 0; i < NI / (3 - PARTS); ++i) load_stencil_y(ld, I0 + i, st[i]);
     __builtin_amdgcn_sched_barrier(0);
 
-    double neq[NV], r[4];
-    {
-        double fd[NV];
+    S (&row)[NX][68] = sh.x[PART];
 #pragma unroll
-        for (int i = 0; i < NV; ++i) fd[i] = (double)f[i];
+    for (int i = 0; i < NI; ++i)
+        if (SX[I0 + i] != 0) row[x_slot(I0 + i) - K0][2 + lane] = f[i];
+    double neq[NI], r[4];
+    {
+        double fd[NI];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) fd[i] = (double)f[i];
         Parity g;
-        to_parity(fd, g);
+        if constexpr (PARTS == 1) to_parity(fd, g);
+        else exchange_half<PART, PARTS>(sh.half[0], fd, g);
         double q[4];
         stage_conserved(g, K, q);
         Macro m;
@@ -161,22 +192,28 @@ __global__ void __launch_bounds__(256) k_stage(const S* __restrict__ fin,
         } else {
             m = macro_of(q[0], q[1], q[2], q[3], K->inv_a);
         }
-        nonequilibrium(g, m, *K, K->a, neq);
+        nonequilibrium<PARTS == 1 ? 0 : PART, PARTS == 1 ? 2 : PART + 1>(g, m, *K, K->a, neq);
     }
+    if (lane < 4 * NX) row[lane >> 2][halo_place()] = halo;
     __builtin_amdgcn_sched_barrier(0);
+    // the row is read by the wave that wrote it, whose LDS operations are in order
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 #pragma unroll
-    for (int i = NV / 2; i < NV; ++i) load_stencil(ld, i, st[i]);
+    for (int i = NI / (3 - PARTS); i < NI; ++i) load_stencil_y(ld, I0 + i, st[i]);
     if constexpr (STAGE2) {
 #pragma unroll
-        for (int i = 0; i < NV; ++i) hb[i] = lb(i, 0, 0);
+        for (int i = 0; i < NI; ++i) hb[i] = lb(I0 + i, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
 
     const bool inside = x < nx;
     char* const o = (char*)fout + (int64_t)y * pitch + (int64_t)x * (int64_t)sizeof(S);
-    double lost[NV];
+    double lost[NI];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
+    for (int j = 0; j < NI; ++j) {
+        const int i = I0 + j;
         A cx, cy, nz;
         if constexpr (sizeof(A) == 4) {
             cx = K->cf[STAGE2][i / 4];
@@ -187,48 +224,84 @@ __global__ void __launch_bounds__(256) k_stage(const S* __restrict__ fin,
             cy = K->cd[STAGE2][4 + i / 4];
             nz = K->cd[STAGE2][8 + (i / 4) % 2];
         }
-        const A fi = (A)f[i];
-        const A adv = stencil_advection<A, S>(i, st[i], fi, cx, cy);
+        const A fi = (A)f[j];
+        if (SX[i] != 0) read_stencil_x(row[x_slot(i) - K0], lane, i, st[j]);
+        const A adv = stencil_advection<A, S>(i, st[j], fi, cx, cy);
         S v;
         if constexpr (COMP) {
             double yv = adv;
-            if (STAGE2) yv += 0.5 * fi + 0.5 * (double)hb[i];
+            if (STAGE2) yv += 0.5 * fi + 0.5 * (double)hb[j];
             else yv += fi;
-            v = (S)fma(nz, neq[i], yv);
-            lost[i] = yv - (double)v;
+            v = (S)fma(nz, neq[j], yv);
+            lost[j] = yv - (double)v;
         } else {
-            const A d = fma(nz, (A)neq[i], adv);
+            const A d = fma(nz, (A)neq[j], adv);
             v = STAGE2 ? fma(A(0.5), fi, d) : fi + d;
-            if (STAGE2) v = fma(A(0.5), hb[i], v);
+            if (STAGE2) v = fma(A(0.5), hb[j], v);
         }
         if (inside) *(S*)(o + i * ld.plane) = v;
     }
     if constexpr (COMP) {
         Parity gl;
-        to_parity(lost, gl);
+        if constexpr (PARTS == 1) to_parity(lost, gl);
+        else exchange_half<PART, PARTS>(sh.half[1], lost, gl);
         double dm[4];
         stage_conserved(gl, K, dm);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 4 / PARTS * PART; k < 4 / PARTS * (PART + 1); ++k) {
             double rk = r[k];
-            if (STAGE2) rk = 0.5 * (double)lb(NV + k, 0, 0) + 0.5 * rk;
+            if (STAGE2) rk = 0.5 * (double)lb(NV + k, 0) + 0.5 * rk;
             if (inside) *(S*)(o + (NV + k) * ld.plane) = (S)(rk + dm[k]);
         }
     }
 }
 
+template <typename S, bool STAGE2, bool COMP, int PARTS>
+__global__ void __launch_bounds__(64 * PARTS) k_stage(const S* __restrict__ fin,
+                                                      const S* __restrict__ base,
+                                                      S* __restrict__ fout,
+                                                      const StageParams* __restrict__ Kd, int nx,
+                                                      int ny, int bc) {
+    __shared__ StageRow<S, COMP, PARTS> row;
+    const uint32_t per_row = (uint32_t)(nx + 63) / 64;
+    const uint32_t b = band_index(blockIdx.x, gridDim.x);
+    const int y = (int)(b / per_row), x0 = (int)(b - (uint32_t)y * per_row) * 64;
+    const StageTable K = (StageTable)(uintptr_t)Kd;
+    if (PARTS == 1 || __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0)
+        stage_part<S, STAGE2, COMP, 0, PARTS>(fin, base, fout, K, nx, ny, bc, x0, y, row);
+    else
+        stage_part<S, STAGE2, COMP, PARTS - 1, PARTS>(fin, base, fout, K, nx, ny, bc, x0, y, row);
+}
+
+template <typename S, bool COMP, int PARTS>
+hipError_t stage_launch_parts(const void* fin, const void* base, void* fout, bool stage2,
+                              const KParams& K, const StageParams* Kd, hipStream_t st) {
+    const dim3 grid((unsigned)((K.nx + 63) / 64) * (unsigned)K.ny), block(64 * PARTS);
+    const int bc = K.bcx | K.bcy << 1;
+    if (stage2)
+        hipLaunchKernelGGL((k_stage<S, true, COMP, PARTS>), grid, block, 0, st, (const S*)fin,
+                           (const S*)base, (S*)fout, Kd, K.nx, K.ny, bc);
+    else
+        hipLaunchKernelGGL((k_stage<S, false, COMP, PARTS>), grid, block, 0, st, (const S*)fin,
+                           (const S*)base, (S*)fout, Kd, K.nx, K.ny, bc);
+    return hipGetLastError();
+}
+
+// Two waves per block up to 3 * 2^15 cells (1.5 one-wave blocks per SIMD): below
+// that a SIMD has one wave, which issues an instruction every five cycles and
+// waits alone, above it the second wave's copy of the moments costs more.  Step
+// of two stages with one / two waves per block:
+//   100^2 mixed 8.3 / 6.8 us, FP64 9.2 / 7.4, compensated 9.8 / 8.3,
+//   256^2 mixed 9.6 / 8.8, FP64 13.1 / 12.1, compensated 11.6 / 11.7,
+//   400^2 mixed 14.2 / 15.3, FP64 23.3 / 24.2, compensated 21.4 / 23.5.
+constexpr int64_t TWO_WAVE_CELLS = 3 << 15;
+
 template <typename S, bool COMP>
 hipError_t stage_launch(const void* fin, const void* base, void* fout, bool stage2,
                         const KParams& K, const StageParams* Kd, hipStream_t st) {
-    const dim3 grid((K.nx + 63) / 64, (K.ny + 3) / 4);
-    const int bc = K.bcx | K.bcy << 1;
-    if (stage2)
-        hipLaunchKernelGGL((k_stage<S, true, COMP>), grid, dim3(256), 0, st, (const S*)fin,
-                           (const S*)base, (S*)fout, Kd, K.nx, K.ny, bc);
-    else
-        hipLaunchKernelGGL((k_stage<S, false, COMP>), grid, dim3(256), 0, st, (const S*)fin,
-                           (const S*)base, (S*)fout, Kd, K.nx, K.ny, bc);
-    return hipGetLastError();
+    return (int64_t)K.nx * K.ny <= TWO_WAVE_CELLS
+               ? stage_launch_parts<S, COMP, 2>(fin, base, fout, stage2, K, Kd, st)
+               : stage_launch_parts<S, COMP, 1>(fin, base, fout, stage2, K, Kd, st);
 }
 
 }  // namespace
