@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include "launch.hpp"
+#include "row_block.hpp"
 #include "step_quad.hpp"
 
 namespace cdbm {
@@ -28,11 +29,12 @@ __device__ __forceinline__ int wrap_near(int i, int n, int bc, int reach) {
 // the 16 x 16 cells around it goes to LDS, stage 1 runs on the tile and the
 // 2-cell strips beside its four sides (128 cells, one quad each), stage 2 on
 // the tile's 64 cells.  The corners of the halo are not needed: the stencils
-// are crosses.  Bound by latencies: of about 7.6 us from launch to launch at
-// 100 x 100 in FP64, 1.9 until f^n is in LDS, 1.6 stage 1 (two waves per
-// SIMD), 0.8 stage 2, the rest between the launches.  One step of 100 x 100 in
-// FP64 14.7 -> 7.6 us against the two single-stage launches; a call of one
-// step on 32 x 32 (mixed) 11.3 -> 8.4 us.
+// are crosses.  Bound by latencies: of about 6.2 us from launch to launch at
+// 100 x 100 in FP64, 1.6 are stage 1 (two waves per SIMD), 0.8 stage 2, the
+// rest until f^n is in LDS and between the launches.  Tiles are numbered in
+// bands (band_index): 100 x 100 FP64 7.6 -> 6.2 us, 128 x 128 mixed 6.5 -> 5.0.
+// One step of 100 x 100 in FP64 14.7 -> 6.2 us against the two launches of one
+// cell per lane; a call of one step on 32 x 32 (mixed) 11.3 -> 8.3 us.
 constexpr int TILE = 8, TW0 = TILE + 8, TN0 = TW0 * TW0, TW1 = TILE + 4, TN1 = TW1 * TW1;
 constexpr int TILE_THREADS = 4 * (TILE * TILE + 8 * TILE);
 
@@ -45,7 +47,9 @@ __global__ void __launch_bounds__(TILE_THREADS) k_tile_step(const S* __restrict_
     __shared__ __attribute__((aligned(32))) S F0[NV * TN0];
     __shared__ __attribute__((aligned(32))) S F1[NV * TN1];
     const int64_t cells = (int64_t)nx * ny;
-    const int x0 = blockIdx.x * TILE, y0 = blockIdx.y * TILE;
+    const uint32_t per_row = (uint32_t)(nx + TILE - 1) / TILE;
+    const uint32_t b = band_index(blockIdx.x, gridDim.x), ty = b / per_row;
+    const int x0 = (int)(b - ty * per_row) * TILE, y0 = (int)ty * TILE;
     const int tid = threadIdx.x, q = tid & 3;
     const QuadLane L = quad_lane(q);
     QuadConst<S> Q;
@@ -136,7 +140,7 @@ __global__ void __launch_bounds__(4 * LINE_CELLS) k_line_steps(const S* __restri
     constexpr int W = LINE_CELLS;
     __shared__ __attribute__((aligned(32))) S F0[NV * W];
     __shared__ __attribute__((aligned(32))) S F1[NV * W];
-    const int x0 = blockIdx.x * (W - 8 * steps) - 4 * steps;
+    const int x0 = (int)band_index(blockIdx.x, gridDim.x) * (W - 8 * steps) - 4 * steps;
     const int tid = threadIdx.x, q = tid & 3, lx = tid >> 2;
     const QuadLane L = quad_lane(q);
     QuadConst<S> Q;
@@ -186,9 +190,9 @@ __global__ void __launch_bounds__(4 * LINE_CELLS) k_line_steps(const S* __restri
 
 // One block per compute unit at most: a block's stages are bound by the
 // latency of two waves per SIMD, and with a second round of blocks the two
-// launches of the single-stage kernels are as fast (mixed / FP64: 128 x 128,
-// 256 blocks, 8 / 11 us against 12 / 15; 160 x 160, 400 blocks, 11 / 17
-// against 12 / 16; 256 x 256 20 / 29 against 15 / 20).
+// launches of the single-stage kernels are faster (mixed / FP64: 128 x 128,
+// 256 blocks, 5.0 / 6.2 us against 6.3 / 7.1; 144 x 144, 324 blocks, 7.9 / 9.9
+// against 7.3 / 8.8; 160 x 160 7.8 / 9.7 against 7.3 / 9.0).
 bool tile_step_fits(const KParams& K) {
     return (int64_t)((K.nx + TILE - 1) / TILE) * ((K.ny + TILE - 1) / TILE) <= device_cus();
 }
@@ -218,7 +222,7 @@ int line_steps_per_launch(const KParams& K) {
 template <typename S>
 hipError_t launch_tile_step(const void* fin, void* f1out, void* fout, const KParams& K,
                             const QuadParams* Qd, hipStream_t st) {
-    const dim3 grid((K.nx + TILE - 1) / TILE, (K.ny + TILE - 1) / TILE);
+    const dim3 grid(((K.nx + TILE - 1) / TILE) * ((K.ny + TILE - 1) / TILE));
     hipLaunchKernelGGL(k_tile_step<S>, grid, dim3(TILE_THREADS), 0, st, (const S*)fin, Qd, K.nx,
                        K.ny, K.bcx | K.bcy << 1, (S*)fout, (S*)f1out);
     return hipGetLastError();
