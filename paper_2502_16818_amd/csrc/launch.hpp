@@ -22,8 +22,6 @@ hipError_t launch_tne(const void* f, double* out12, bool raw, const KParams& K, 
 template <typename S>
 hipError_t launch_totals(const void* f, double* partials, int nblocks, double* out4,
                          const KParams& K, hipStream_t st);
-hipError_t launch_sum_partials(const double* part, int nblocks, int ncomp, double* out,
-                               hipStream_t st);
 template <typename S>
 hipError_t launch_stage(const void* fin, const void* base, void* fout, bool stage2,
                         const KParams& K, const StageParams* Kd, hipStream_t st);
