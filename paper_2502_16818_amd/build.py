@@ -28,6 +28,7 @@ SOURCES = [
     "kernels_step.hip",
     "kernels_stage.hip",
     "kernels_quad.hip",
+    "kernels_march.hip",
     "kernels_adjoint.hip",
     "kernels_batch.hip",
 ]
@@ -42,6 +43,7 @@ FLAGS = [
 # further flags of one source: kernels of a few microseconds get their
 # arguments in registers instead of waiting for a load from a cold cache
 EXTRA = {
+    "kernels_march.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
     "kernels_quad.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
     "kernels_stage.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
 }

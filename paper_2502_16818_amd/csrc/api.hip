@@ -195,6 +195,11 @@ namespace {
 // 34.7 / 44.6, 600^2 45.4 / 45.0, 660^2 54.5 / 45.7.
 constexpr int64_t SPLIT_STEP_CELLS_MIXED = 600000;
 constexpr int64_t SPLIT_STEP_CELLS_FP64 = 350000;
+// From this size on the fused FP64 step marches (kernels_march.hip); below, its
+// pieces of a few rows read most rows twice.  Strips with rings / marching:
+// 724^2 56.8 / 60.5 us, 1000 x 777 76.0 / 72.4, 1448^2 177 / 155, 2048 x 1536
+// 253 / 200.
+constexpr int64_t MARCH_STEP_CELLS = 700000;
 
 hipError_t step_once(const cdbm_handle* h, const void* fin, void* fout, hipStream_t st) {
     if (h->tile)
@@ -212,6 +217,8 @@ hipError_t step_once(const cdbm_handle* h, const void* fin, void* fout, hipStrea
         return mixed(h) ? launch_stage<float>(h->stage, fin, fout, true, h->k, h->sdev, st)
                         : launch_stage<double>(h->stage, fin, fout, true, h->k, h->sdev, st);
     }
+    if (!mixed(h) && h->cells >= MARCH_STEP_CELLS)
+        return launch_step_march(fin, fout, h->k, h->sdev, st);
     return mixed(h) ? launch_step_fused<float>(fin, fout, h->k, h->kdev, st)
                     : launch_step_fused<double>(fin, fout, h->k, h->kdev, st);
 }

@@ -67,6 +67,10 @@ template <typename S>
 hipError_t launch_line_steps(const void* fin, void* fout, int steps, const KParams& K,
                              const QuadParams* Qd, hipStream_t st);
 
+// The fused FP64 step as marching strips (kernels_march.hip), for large grids.
+hipError_t launch_step_march(const void* fin, void* fout, const KParams& K, const StageParams* Kd,
+                             hipStream_t st);
+
 // Adjoint (kernels_adjoint.hip).  tau_part: one double per 64 cells of a row
 // (stage_adjoint_blocks), the sums of the launch's tau term, written or
 // (tau_add) added to what it holds.
