@@ -288,11 +288,9 @@ int cdbm_create(const cdbm_params* p, cdbm_handle** out) {
     }
     struct {
         QuadParams quad;
-        StageParams stage;
         KParams k;
     } consts;
     build_quad(h->k, consts.quad);
-    build_stage(h->k, consts.stage);
     consts.k = h->k;
     if (ensure_buffer(h, &h->scratch) != CDBM_OK ||
         ((h->split || h->two) && ensure_buffer(h, &h->stage) != CDBM_OK) ||
@@ -304,8 +302,8 @@ int cdbm_create(const cdbm_params* p, cdbm_handle** out) {
         cdbm_destroy(h);
         return fail(CDBM_ENOMEM, "device allocation failed");
     }
-    h->sdev = (StageParams*)((char*)h->qdev + offsetof(decltype(consts), stage));
     h->kdev = (KParams*)((char*)h->qdev + offsetof(decltype(consts), k));
+    h->sdev = &h->kdev->s;
     e = hipMemcpy(h->qdev, &consts, sizeof(consts), hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemset(h->tau_acc, 0, sizeof(double) * stage_adjoint_blocks(h->k));

@@ -83,6 +83,31 @@ bool finite_pos(double x) { return std::isfinite(x) && x > 0.0; }
 
 double extra_dof(double gamma) { return 2.0 / (gamma - 1.0) - 2.0; }
 
+static void build_stage(const KParams& k, StageParams& m) {
+    std::memset(&m, 0, sizeof(m));
+    static const int en[4] = {0, 2, 3, 5};
+    for (int g = 0; g < 4; ++g) {
+        m.jv[g] = k.jx[g];
+        m.en[g] = k.en[en[g]];
+        for (int h = 0; h < 2; ++h) {
+            // velocities 0, 4, 8, 12 move towards larger x, 1, 4, 9, 12 towards larger y
+            const int ix = 4 * g, iy = 4 * g + (g % 2 == 0 ? 1 : 0);
+            const double half = h ? 0.5 : 1.0;
+            m.cd[h][g] = half * k.cx[ix];
+            m.cd[h][4 + g] = half * k.cy[iy];
+            if (g < 2) m.cd[h][8 + g] = -k.z * half * (g ? 0.25 : 0.5);
+        }
+        for (int c = 0; c < 4; ++c) m.ioe[g][c] = k.ioe[g][c];
+    }
+    for (int h = 0; h < 2; ++h)
+        for (int c = 0; c < 10; ++c) m.cf[h][c] = (float)m.cd[h][c];
+    m.inv_a = k.inv_a;
+    m.a = k.a;
+    std::memcpy(m.eep, k.eep, sizeof(m.eep));
+    std::memcpy(m.ees, k.ees, sizeof(m.ees));
+    std::memcpy(m.ioo, k.ioo, sizeof(m.ioo));
+}
+
 int build_params(const cdbm_params& p, KParams& k, std::string& err) {
     std::memset(&k, 0, sizeof(k));
     char buf[256];
@@ -286,55 +311,18 @@ int build_params(const cdbm_params& p, KParams& k, std::string& err) {
         k.eta2[i] = eta[i] * eta[i];
         k.cx[i] = -p.dt * vx[i] / p.dx;
         k.cy[i] = -p.dt * vy[i] / p.dy;
-        k.cxf[i] = (float)k.cx[i];
-        k.cyf[i] = (float)k.cy[i];
-        k.cxh[i] = 0.5 * k.cx[i];
-        k.cyh[i] = 0.5 * k.cy[i];
-        k.cxhf[i] = (float)k.cxh[i];
-        k.cyhf[i] = (float)k.cyh[i];
     }
     k.a = 2.0 + (p.dof_given ? p.extra_dof : extra_dof(p.gamma));
     k.inv_a = 1.0 / k.a;
     k.z = p.dt / p.tau;
-    for (int h = 0; h < 2; ++h)
-        for (int grp = 0; grp < 2; ++grp) {
-            k.nzq[h][grp] = -k.z * (h ? 0.5 : 1.0) * (grp ? 0.25 : 0.5);
-            k.nzqf[h][grp] = (float)k.nzq[h][grp];
-        }
     k.dt = p.dt;
     k.tau = p.tau;
     k.nx = p.nx;
     k.ny = p.ny;
     k.bcx = p.bc_x;
     k.bcy = p.bc_y;
+    build_stage(k, k.s);
     return CDBM_OK;
-}
-
-void build_stage(const KParams& k, StageParams& m) {
-    std::memset(&m, 0, sizeof(m));
-    static const int en[4] = {0, 2, 3, 5};
-    for (int g = 0; g < 4; ++g) {
-        m.jv[g] = k.jx[g];
-        m.en[g] = k.en[en[g]];
-        for (int h = 0; h < 2; ++h) {
-            // velocities 0, 4, 8, 12 move towards larger x, 1, 4, 9, 12 towards larger y
-            const int ix = 4 * g, iy = 4 * g + (g % 2 == 0 ? 1 : 0);
-            m.cd[h][g] = h ? k.cxh[ix] : k.cx[ix];
-            m.cd[h][4 + g] = h ? k.cyh[iy] : k.cy[iy];
-            m.cf[h][g] = h ? k.cxhf[ix] : k.cxf[ix];
-            m.cf[h][4 + g] = h ? k.cyhf[iy] : k.cyf[iy];
-            if (g < 2) {
-                m.cd[h][8 + g] = k.nzq[h][g];
-                m.cf[h][8 + g] = k.nzqf[h][g];
-            }
-        }
-        for (int c = 0; c < 4; ++c) m.ioe[g][c] = k.ioe[g][c];
-    }
-    m.inv_a = k.inv_a;
-    m.a = k.a;
-    std::memcpy(m.eep, k.eep, sizeof(m.eep));
-    std::memcpy(m.ees, k.ees, sizeof(m.ees));
-    std::memcpy(m.ioo, k.ioo, sizeof(m.ioo));
 }
 
 void build_quad(const KParams& k, QuadParams& r) {
@@ -350,7 +338,7 @@ void build_quad(const KParams& k, QuadParams& r) {
         r.lane.ay[p] = k.cy[8 * p + 1];
         r.lane.dx[p] = k.cx[8 * p + 4];
         r.lane.dy[p] = k.cy[8 * p + 4];
-        r.lane.nz[p] = k.nzq[0][p];
+        r.lane.nz[p] = k.s.cd[0][8 + p];
     }
     for (int p = 0; p < 2; ++p) {
         for (int c = 0; c < 4; ++c) {

@@ -33,6 +33,21 @@ constexpr int NV = 16;
 constexpr int SX[NV] = {1, 0, -1, 0, 1, -1, -1, 1, 1, 0, -1, 0, 1, -1, -1, 1};
 constexpr int SY[NV] = {0, 1, 0, -1, 1, 1, -1, -1, 0, 1, 0, -1, 1, 1, -1, -1};
 
+// The constants of a stage, packed
+// in the order of use, so that they come in a few wide scalar loads: the
+// groups' speeds (the rows of both momenta), the energy row, 1 / (D + I),
+// D + I, then eep, ees, ioo and ioe (ieo is its mirror image); for the two
+// Runge-Kutta stages the NND coefficients of velocities towards larger indices
+// (groups a .. d along x, then along y) and the relaxation factors of the axis
+// and the diagonal groups.
+struct alignas(64) StageParams {
+    double jv[4], en[4];
+    double inv_a, a, eep[2][6], ees[2][4], ioo[2][2];
+    double ioe[4][4];
+    double cd[2][10];
+    float cf[2][10];
+};
+
 // Constants handed by value to every kernel.
 struct KParams {
     // Inverses of the parity blocks of M0.  Output rows are pre-multiplied by
@@ -59,19 +74,12 @@ struct KParams {
     double jx[4], jy[4], en[6];
     double vx[NV], vy[NV], eta2[NV];
     double cx[NV], cy[NV];     // -dt v_ix / dx and -dt v_iy / dy
-    float cxf[NV], cyf[NV];
-    double cxh[NV], cyh[NV];   // the same halved (the second Runge-Kutta stage)
-    float cxhf[NV], cyhf[NV];
     double a;                  // D + I
     double inv_a;              // 1 / (D + I)
     double z;                  // dt / tau
-    // -z/2 (axis groups) and -z/4 (diagonal groups) for the first Runge-Kutta
-    // stage, then halved for the second: the factors that turn the output of
-    // nonequilibrium() into -z (f - f^eq).
-    double nzq[2][2];
-    float nzqf[2][2];
     double dt, tau;
     int32_t nx, ny, bcx, bcy;
+    StageParams s;             // the same constants as a stage reads them
 };
 
 // The constants of the four-lanes-per-cell kernels (step_quad.hpp).
@@ -100,22 +108,6 @@ struct alignas(64) QuadParams {
 static_assert(sizeof(QuadParams::Lane) == 5 * 64 && sizeof(QuadParams::Shared) == 5 * 64,
               "quad_const() touches each 64-byte line");
 
-// The constants of a stage with one cell per lane (kernels_stage.hip), packed
-// in the order of use, so that they come in a few wide scalar loads: the
-// groups' speeds (the rows of both momenta), the energy row, 1 / (D + I),
-// D + I, then eep, ees, ioo and ioe (ieo is its mirror image); for the two
-// Runge-Kutta stages the NND coefficients of velocities towards larger indices
-// (groups a .. d along x, then along y) and the relaxation factors of the axis
-// and the diagonal groups.
-struct alignas(64) StageParams {
-    double jv[4], en[4];
-    double inv_a, a, eep[2][6], ees[2][4], ioo[2][2];
-    double ioe[4][4];
-    double cd[2][10];
-    float cf[2][10];
-};
-
-void build_stage(const KParams& k, StageParams& m);
 void build_quad(const KParams& k, QuadParams& q);
 
 // Validate p and fill k.  Returns CDBM_OK or an error code with a message.

@@ -57,24 +57,13 @@ struct FusedGeom<double> {
     static_assert(W0 == TX + 8 && W1 >= TX + 4 && W1 <= 64, "one column per lane");
 };
 
-// NND coefficients -dt v_ir / dr of a stage: HALF selects the halved ones of
-// the second Runge-Kutta stage.
+// The groups' NND coefficients -dt v_ir / dr of a stage (velocities towards
+// larger indices) and its relaxation factors -z/2 (axis groups) and -z/4
+// (diagonal groups), all halved in the second stage.
 template <typename S, bool HALF>
-__device__ __forceinline__ S stage_coef_x(const KParams& K, int i, int z) {
-    if constexpr (sizeof(S) == 4) return HALF ? K.cxhf[i + z] : K.cxf[i + z];
-    else return HALF ? K.cxh[i + z] : K.cx[i + z];
-}
-template <typename S, bool HALF>
-__device__ __forceinline__ S stage_coef_y(const KParams& K, int i, int z) {
-    if constexpr (sizeof(S) == 4) return HALF ? K.cyhf[i + z] : K.cyf[i + z];
-    else return HALF ? K.cyh[i + z] : K.cy[i + z];
-}
-
-// -z/2 (axis groups, grp 0) or -z/4 (diagonal groups, grp 1) of a stage.
-template <typename S, bool HALF>
-__device__ __forceinline__ S stage_relax(const KParams& K, int grp, int z) {
-    if constexpr (sizeof(S) == 4) return K.nzqf[HALF][grp + z];
-    else return K.nzq[HALF][grp + z];
+__device__ __forceinline__ S stage_coef(const StageParams& K, int c) {
+    if constexpr (sizeof(S) == 4) return K.cf[HALF][c];
+    else return K.cd[HALF][c];
 }
 
 // Reads of one ring buffer around one cell.  Offsets are compile-time after
@@ -135,6 +124,7 @@ __device__ __forceinline__ double from_right(double v) { return shift_lanes<0x13
 template <typename S, bool HALF, class Ld, bool XLANE = false>
 __device__ __forceinline__ void stage_cell_k(const Ld& ld, const KParams& K, S out[NV]) {
     const int z = opaque_zero();
+    const StageParams& C = *(const StageParams*)((const char*)&K.s + z);
     S f[NV];
     double fd[NV];
 #pragma unroll
@@ -144,34 +134,45 @@ __device__ __forceinline__ void stage_cell_k(const Ld& ld, const KParams& K, S o
     }
     Parity g;
     to_parity(fd, g);
-    const Macro m = macro_from_parity(g, K, (&K.inv_a)[z], z);
+    const double rho = ((g.ee[0] + g.ee[1]) + (g.ee[2] + g.ee[3])) + (g.ee[4] + g.ee[5]);
+    double jx = 0.0, jy = 0.0, e2 = 0.0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        jx = fma(C.jv[c], g.oe[c], jx);
+        jy = fma(C.jv[c], g.eo[c], jy);
+    }
+    constexpr int group[6] = {0, 0, 1, 2, 2, 3};
+#pragma unroll
+    for (int c = 0; c < 6; ++c) e2 = fma(C.en[group[c]], g.ee[c], e2);
+    const Macro m = macro_of(rho, jx, jy, e2, C.inv_a);
     double neq[NV];
-    nonequilibrium(g, m, K, (&K.a)[z], neq, z);
-    // -z / k of the stage, k = 2 (axis groups) or 4 (diagonal groups)
-    const S nza = stage_relax<S, HALF>(K, 0, z), nzd = stage_relax<S, HALF>(K, 1, z);
+    nonequilibrium(g, m, C, C.a, neq);
+    S cx[4], cy[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        cx[c] = stage_coef<S, HALF>(C, c);
+        cy[c] = stage_coef<S, HALF>(C, 4 + c);
+    }
+    const S nza = stage_coef<S, HALF>(C, 8), nzd = stage_coef<S, HALF>(C, 9);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
+        const int gr = i / 4;
         S adv = S(0);
+        if (SY[i] > 0)
+            adv = cy[gr] * nnd_pos<S>(ld(i, 0, -2), ld(i, 0, -1), f[i], ld(i, 0, 1));
+        else if (SY[i] < 0)
+            adv = -cy[gr] * nnd_neg<S>(ld(i, 0, -1), f[i], ld(i, 0, 1), ld(i, 0, 2));
         if constexpr (XLANE) {
             if (SX[i] != 0) {
                 const S dl = f[i] - ld(i, -1, 0), dr = ld(i, 1, 0) - f[i];
                 const S M = minmod(dr, dl);
-                const S cx = stage_coef_x<S, HALF>(K, i, z);
-                if (SX[i] > 0) adv = cx * (dl + S(0.5) * (M - from_left(M)));
-                else adv = cx * (dr - S(0.5) * (from_right(M) - M));
+                if (SX[i] > 0) adv = fma(cx[gr], dl + S(0.5) * (M - from_left(M)), adv);
+                else adv = fma(-cx[gr], dr - S(0.5) * (from_right(M) - M), adv);
             }
         } else if (SX[i] > 0)
-            adv = stage_coef_x<S, HALF>(K, i, z) *
-                  nnd_pos<S>(ld(i, -2, 0), ld(i, -1, 0), f[i], ld(i, 1, 0));
+            adv = fma(cx[gr], nnd_pos<S>(ld(i, -2, 0), ld(i, -1, 0), f[i], ld(i, 1, 0)), adv);
         else if (SX[i] < 0)
-            adv = stage_coef_x<S, HALF>(K, i, z) *
-                  nnd_neg<S>(ld(i, -1, 0), f[i], ld(i, 1, 0), ld(i, 2, 0));
-        if (SY[i] > 0)
-            adv += stage_coef_y<S, HALF>(K, i, z) *
-                   nnd_pos<S>(ld(i, 0, -2), ld(i, 0, -1), f[i], ld(i, 0, 1));
-        else if (SY[i] < 0)
-            adv += stage_coef_y<S, HALF>(K, i, z) *
-                   nnd_neg<S>(ld(i, 0, -1), f[i], ld(i, 0, 1), ld(i, 0, 2));
+            adv = fma(-cx[gr], nnd_neg<S>(ld(i, -1, 0), f[i], ld(i, 1, 0), ld(i, 2, 0)), adv);
         const S d = fma((i & 4) ? nzd : nza, (S)neq[i], adv);
         out[i] = HALF ? fma(S(0.5), f[i], d) : f[i] + d;
     }
