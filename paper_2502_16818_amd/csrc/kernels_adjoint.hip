@@ -165,19 +165,24 @@ __device__ __forceinline__ EqTranspose eq_transpose(const Macro& m, const Parity
 // PART = 1: c and d); of the pointwise part wave 0 forms the equilibrium
 // transpose, handed to the other through LDS, and wave 1 the tau term.
 //
-// The return path of the vector loads bounds it (a 64-bit load of a wave takes
-// 16 cycles of a CU whether it hits or not, and with every stencil offset loaded
-// that path was 86 % busy): the x offsets therefore come from the waves' own
-// centres in LDS, with one load for the columns on either side, and only the y
-// offsets are loaded.  Time of a step's two stages (the four-wave block with
-// both lines loaded / one wave per row, loaded / two waves, loaded / this):
-//   256^2 mixed 31.6 / 29.9 / 22.9 / 21.2 us, FP64 35.0 / 33.4 / 27.3 / 23.5,
-//   1000 x 777 mixed 297 / 207 / 200 / 206, FP64 338 / 254 / 289 / 227,
-//   1800^2 FP64 1474 / 1194 / 1282 / 912.
+// Bound by the return path of the vector loads (a 64-bit load of a wave takes
+// 16 cycles of a CU whether it hits or not; with every stencil offset loaded
+// that path was 86 % busy) and, on grids of a few waves per SIMD, by latencies.
+// Therefore the x offsets come from the waves' own centres in LDS, with one
+// load for the columns on either side; what a wave reads once (add, the tau
+// slot) is requested with the centres, and the y offsets of four velocities
+// ahead; the fluxes are formed before the waves meet for the equilibrium
+// transpose.  The blocks are numbered in bands (band_index), so that the rows
+// y +- 2 are in the block's own L2.  Time of a step's two stages (the four-wave
+// block with both lines loaded / one wave per row, loaded / two waves, loaded /
+// x through LDS and bands / this):
+//   256^2 mixed 31.6 / 29.9 / 22.9 / 21.2 / 18.5 us, FP64 35.0 / 33.4 / 27.3 / 23.5 / 21.8,
+//   1000 x 777 mixed 297 / 207 / 200 / 206 / 179, FP64 338 / 254 / 289 / 227 / 204,
+//   1800^2 FP64 1474 / 1194 / 1282 / 912 / 835.
 // Two rows per block (four waves) cost up to 16 % more on large grids and gain
-// at most 2 % on small ones.  The blocks are numbered in bands (band_index), so
-// that the rows y +- 2 are in the block's own L2: without it 256^2 FP64 25.8,
-// 1800^2 FP64 1060 us.
+// at most 2 % on small ones; without the bands 256^2 FP64 took 10 % more; y
+// offsets 2 / 4 / 8 velocities ahead: 1000 x 777 FP64 211 / 204 / 206 us,
+// 256^2 mixed 18.8 / 18.5 / 19.8.
 struct AdjointArgs {
     int nx, ny, bc;
     double w_in, w_add, z, dt_tau2;
@@ -200,7 +205,7 @@ __device__ __forceinline__ void stage_adjoint_part(const S* __restrict__ g,
                                                    const AdjointArgs& p, int x0, int y,
                                                    double* __restrict__ tau_slot, int acc,
                                                    AdjointRow<S>& sh) {
-    constexpr int NI = NV / 2, I0 = PART * NI, I1 = I0 + NI, NX = NVX / 2, K0 = PART * NX;
+    constexpr int NI = NV / 2, I0 = PART * NI, I1 = I0 + NI, AHEAD = 4, NX = NVX / 2, K0 = PART * NX;
     const int nx = p.nx, ny = p.ny, bc = p.bc, lane = threadIdx.x & 63, x = x0 + lane;
     ColumnLd<S> lg;
     ColumnLd<double> la;
@@ -215,9 +220,20 @@ __device__ __forceinline__ void stage_adjoint_part(const S* __restrict__ g,
     }
     const S hg = halo_value<S>(g, K0, NX, x0, y, nx, ny, !(bc & 1), false);
     const double ha = halo_value<double>(a, K0, NX, x0, y, nx, ny, !(bc & 1), true);
-    AdjointStencil<S> st[3];
-    load_adjoint_stencil(lg, la, I0, st[0]);
-    load_adjoint_stencil(lg, la, I0 + 1, st[1]);
+    AdjointStencil<S> st[AHEAD + 1];
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) load_adjoint_stencil(lg, la, I0 + i, st[i]);
+    const bool inside = x < nx;
+    const int64_t at = (int64_t)y * nx + min(x, nx - 1), cells = (int64_t)nx * ny;
+    double prior[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) prior[i] = 0.0;
+    if (p.w_add != 0.0) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) prior[i] = add[(I0 + i) * cells + at];
+    }
+    double tau_before = 0.0;
+    if (PART == 1 && acc) tau_before = *tau_slot;
     __builtin_amdgcn_sched_barrier(0);
 
     S (&tg)[NX][68] = sh.g[PART];
@@ -292,32 +308,23 @@ __device__ __forceinline__ void stage_adjoint_part(const S* __restrict__ g,
             double v = x < nx ? p.dt_tau2 * d * p.w_in : 0.0;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-            if (lane == 0) *tau_slot = acc ? *tau_slot + v : v;
+            if (lane == 0) *tau_slot = acc ? tau_before + v : v;
         }
     }
-    __syncthreads();
-    if constexpr (PART == 1)
-        eq = EqTranspose{sh.eq[0][lane], sh.eq[1][lane], sh.eq[2][lane], sh.eq[3][lane]};
     // 0 where a face of the cell is the edge of a zero-gradient side
     const double kxm = (bc & 1) && x == 0 ? 0.0 : 1.0, kxp = (bc & 1) && x == nx - 1 ? 0.0 : 1.0;
     const double kym = (bc & 2) && y == 0 ? 0.0 : 1.0, kyp = (bc & 2) && y == ny - 1 ? 0.0 : 1.0;
     const double w1 = p.w_in * (1.0 - p.z), w2 = p.w_in * p.z;
-    double cx[2], cy[2], vg[2], base[2];
+    double cx[2], cy[2], flux[NI];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int gr = 2 * PART + k;
         cx[k] = K->cd[0][gr];
         cy[k] = K->cd[0][4 + gr];
-        vg[k] = K->jv[gr];
-        base[k] = fma(eq.ce, K->en[gr], eq.c0);
     }
-    const bool inside = x < nx;
-    const int64_t at = (int64_t)y * nx + min(x, nx - 1), cells = (int64_t)nx * ny;
 #pragma unroll
     for (int i = I0; i < I1; ++i) {
-        if (i + 2 < I1) load_adjoint_stencil(lg, la, i + 2, st[(i + 2 - I0) % 3]);
-        double prior = 0.0;
-        if (p.w_add != 0.0) prior = add[i * cells + at];
+        if (i + AHEAD < I1) load_adjoint_stencil(lg, la, i + AHEAD, st[(i + AHEAD - I0) % (AHEAD + 1)]);
         __builtin_amdgcn_sched_barrier(0);
         const int k = (i - I0) / 4;
         const double aci = ac[i - I0];
@@ -334,18 +341,26 @@ __device__ __forceinline__ void stage_adjoint_part(const S* __restrict__ g,
             if (SX[i] > 0) adv = cx[k] * nnd_transpose<true, S>(f, A, kxm, kxp);
             else adv = -cx[k] * nnd_transpose<false, S>(f, A, kxm, kxp);
         }
-        AdjointStencil<S>& s = st[(i - I0) % 3];
+        AdjointStencil<S>& s = st[(i - I0) % (AHEAD + 1)];
         s.f[2] = gc[i - I0];
         s.a[2] = aci;
         if (SY[i] > 0) adv = fma(cy[k], nnd_transpose<true, S>(s.f, s.a, kym, kyp), adv);
         else if (SY[i] < 0) adv = fma(-cy[k], nnd_transpose<false, S>(s.f, s.a, kym, kyp), adv);
-        double ceq = base[k];
-        if (SX[i] != 0) ceq = fma(SX[i] > 0 ? vg[k] : -vg[k], eq.cx, ceq);
-        if (SY[i] != 0) ceq = fma(SY[i] > 0 ? vg[k] : -vg[k], eq.cy, ceq);
-        double r = fma(p.w_in, adv, fma(w1, aci, w2 * ceq));
-        r = fma(p.w_add, prior, r);
-        if (inside) out[i * cells + at] = r;
+        flux[i - I0] = adv;
         __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+    if constexpr (PART == 1)
+        eq = EqTranspose{sh.eq[0][lane], sh.eq[1][lane], sh.eq[2][lane], sh.eq[3][lane]};
+#pragma unroll
+    for (int i = I0; i < I1; ++i) {
+        const double vg = K->jv[i / 4];
+        double ceq = fma(eq.ce, K->en[i / 4], eq.c0);
+        if (SX[i] != 0) ceq = fma(SX[i] > 0 ? vg : -vg, eq.cx, ceq);
+        if (SY[i] != 0) ceq = fma(SY[i] > 0 ? vg : -vg, eq.cy, ceq);
+        double r = fma(p.w_in, flux[i - I0], fma(w1, ac[i - I0], w2 * ceq));
+        r = fma(p.w_add, prior[i - I0], r);
+        if (inside) out[i * cells + at] = r;
     }
 }
 
