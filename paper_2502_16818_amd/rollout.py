@@ -10,8 +10,8 @@ initial-equilibrium adjoint maps dL/df0 to the initial fields.  Forward
 states are checkpointed every `every` steps; the backward pass recomputes
 the states of one segment at a time from its checkpoint, and, while a
 segment's first Runge-Kutta stages fit in KEEP_STAGE_BYTES, keeps them
-(cdbm_steps_keep_stages) so that the step adjoints need not recompute them
-(cdbm_steps_adjoint_stages; the gradients are the same bit for bit).  With
+(cdbm_step_keep_stage) so that the step adjoints need not recompute them
+(cdbm_step_adjoint_stage; the gradients are the same bit for bit).  With
 kept stages, two buffer sets let the next segment's recompute run on a
 second stream while the current segment's step adjoints run (the two kinds
 of launch are short on small grids and leave the GPU idle on their own).
@@ -107,34 +107,35 @@ def _reverse_kept(s: Solver, segs, nmax: int, lam, lam_next):
     main = torch.cuda.current_stream()
     side = torch.cuda.Stream()
     side.wait_stream(main)   # checkpoints and buffers were written on main
-    sets = [([s.empty_f() for _ in range(nmax - 1)], [s.empty_f() for _ in range(nmax)])
-            for _ in range(2)]
+    sets = [([s.empty_f() for _ in range(nmax)], [s.empty_f() for _ in range(nmax)],
+             s.empty_f()) for _ in range(2)]
     ready = [torch.cuda.Event(), torch.cuda.Event()]
     free = [None, None]
 
-    def segment(k):
-        (_, n), ck = segs[k]
-        states, stages = sets[k % 2]
-        return [ck] + states[:n - 1], stages[:n]
-
     def recompute(k):
+        (_, n), ck = segs[k]
+        states, stages, spare = sets[k % 2]
         with torch.cuda.stream(side):
             if free[k % 2] is not None:
                 side.wait_event(free[k % 2])
-            s.steps_keep_stages(*segment(k))
+            states[0].copy_(ck)
+            for j in range(n):
+                s.step_keep_stage(states[j], stages[j], states[j + 1] if j + 1 < n else spare)
             ready[k % 2].record(side)
 
     recompute(0)
     for k in range(len(segs)):
+        if k + 1 < len(segs):
+            recompute(k + 1)
+        (_, n), _ = segs[k]
+        states, stages, _ = sets[k % 2]
         main.wait_event(ready[k % 2])
-        lam, lam_next = s.steps_adjoint_stages(*segment(k), lam, lam_next)
+        for j in reversed(range(n)):
+            s.step_adjoint(states[j], lam, lam_next, f1=stages[j], defer_tau=True)
+            lam, lam_next = lam_next, lam
         done = torch.cuda.Event()
         done.record(main)
         free[k % 2] = done
-        # after the launches of segment k, which the host is quicker to queue
-        # than the GPU to run; its buffer set was last read by segment k - 1
-        if k + 1 < len(segs):
-            recompute(k + 1)
     return lam
 
 
