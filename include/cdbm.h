@@ -250,6 +250,16 @@ int cdbm_step_adjoint(cdbm_handle* h, const void* f_n, const void* lam_np1, void
 int cdbm_step_keep_stage(cdbm_handle* h, const void* f_in, void* f1_out, void* f_out,
                          void* stream);
 
+/* nsteps consecutive steps from f[0] with their first stages: f1[j] =
+ * f[j] + dt L(f[j]) for every step j, and f[j + 1] is step j's result for
+ * j + 1 < nsteps (the last step's result is not formed).  f and f1: host
+ * arrays of nsteps device buffers as in cdbm_step_keep_stage, pairwise
+ * non-overlapping; only f[0] is read before it is written.  The same values
+ * as nsteps calls of cdbm_step_keep_stage bit for bit, and the same freedom to
+ * run beside the handle's step adjoints. */
+int cdbm_steps_keep_stages(cdbm_handle* h, void* const* f, void* const* f1, int nsteps,
+                           void* stream);
+
 /* cdbm_step_adjoint with the first Runge-Kutta stage of the step supplied
  * instead of recomputed: f1 = f_n + dt L(f_n) (device [16][ny][nx], handle's
  * precision), as cdbm_step_keep_stage writes it.  Same arguments, contract
@@ -257,6 +267,14 @@ int cdbm_step_keep_stage(cdbm_handle* h, const void* f_in, void* f1_out, void* f
  * lam_n must not overlap f1 either.  Saves one single-stage launch. */
 int cdbm_step_adjoint_stage(cdbm_handle* h, const void* f_n, const void* f1,
                             const void* lam_np1, void* lam_n, double* dL_dtau, void* stream);
+
+/* nsteps calls of cdbm_step_adjoint_stage with dL_dtau = NULL, from step
+ * nsteps - 1 down to step 0 (f, f1 as cdbm_steps_keep_stages leaves them):
+ * the adjoint vector of the state after the last step in lam[0], that of f[0]
+ * in lam[nsteps % 2] afterwards; both buffers are overwritten (each once or
+ * more when nsteps > 1). */
+int cdbm_steps_adjoint_stages(cdbm_handle* h, void* const* f, void* const* f1, int nsteps,
+                              void* const* lam, void* stream);
 
 /* *dL_dtau += the sum, in a fixed order, of the dL/dtau terms that step
  * adjoints called with dL_dtau = NULL have added to the handle's accumulator

@@ -26,6 +26,7 @@ EXPORTS = (
     "cdbm_step", "cdbm_moments", "cdbm_tne", "cdbm_tne_raw", "cdbm_conserved_totals",
     "cdbm_step_adjoint",
     "cdbm_step_keep_stage", "cdbm_step_adjoint_stage", "cdbm_tau_collect",
+    "cdbm_steps_keep_stages", "cdbm_steps_adjoint_stages",
     "cdbm_init_adjoint", "cdbm_moments_adjoint", "cdbm_batch_create", "cdbm_batch_destroy",
     "cdbm_batch_init", "cdbm_batch_step", "cdbm_conserved_totals_static",
     "cdbm_batch_get_launch", "cdbm_batch_set_launch", "cdbm_batch_autotune",
@@ -91,6 +92,8 @@ def load() -> ctypes.CDLL:
         "cdbm_step_adjoint": ([_vp, _vp, _vp, _vp, _vp, _vp], _i32),
         "cdbm_step_keep_stage": ([_vp, _vp, _vp, _vp, _vp], _i32),
         "cdbm_step_adjoint_stage": ([_vp] * 7, _i32),
+        "cdbm_steps_keep_stages": ([_vp, _vp, _vp, _i32, _vp], _i32),
+        "cdbm_steps_adjoint_stages": ([_vp, _vp, _vp, _i32, _vp, _vp], _i32),
         "cdbm_tau_collect": ([_vp, _vp, _vp], _i32),
         "cdbm_init_adjoint": ([_vp] * 11, _i32),
         "cdbm_moments_adjoint": ([_vp] * 8, _i32),
@@ -140,6 +143,11 @@ def _ptr(t: Optional[torch.Tensor], dtype: Optional[torch.dtype] = None,
     if numel is not None and t.numel() < numel:
         raise ValueError(f"CDBM buffer has {t.numel()} elements, the call needs {numel}")
     return t.data_ptr()
+
+
+def _ptrs(addresses, n: int):
+    """A C array of n buffer addresses."""
+    return (ctypes.c_void_p * n)(*addresses)
 
 
 def make_params(nx, ny, dx, dy, dt, tau, gamma, v, eta, bc_x=PERIODIC, bc_y=PERIODIC,
@@ -232,6 +240,26 @@ class Solver:
         _check(load().cdbm_step_keep_stage(self._h, self._f(f_in), self._f(f1_out),
                                            self._f(f_out), _stream()), "cdbm_step_keep_stage")
         return f1_out, f_out
+
+    def steps_keep_stages(self, states: Sequence[torch.Tensor], stages: Sequence[torch.Tensor]):
+        """len(stages) steps from states[0]: step j's first stage into stages[j]
+        and its result into states[j + 1] (the last result is not formed)."""
+        n = len(stages)
+        _check(load().cdbm_steps_keep_stages(self._h, _ptrs(map(self._f, states[:n]), n),
+                                             _ptrs(map(self._f, stages), n), n, _stream()),
+               "cdbm_steps_keep_stages")
+
+    def steps_adjoint_stages(self, states: Sequence[torch.Tensor], stages: Sequence[torch.Tensor],
+                             lam: torch.Tensor, other: torch.Tensor):
+        """Transposes of the steps of steps_keep_stages, the last first, with
+        deferred tau terms: lam, the adjoint vector after the last step, to that
+        of states[0].  Returns (result, the other buffer); both are overwritten."""
+        n = len(stages)
+        _check(load().cdbm_steps_adjoint_stages(self._h, _ptrs(map(self._f, states[:n]), n),
+                                                _ptrs(map(self._f, stages), n), n,
+                                                _ptrs(map(self._lam, (lam, other)), 2), _stream()),
+               "cdbm_steps_adjoint_stages")
+        return (other, lam) if n % 2 else (lam, other)
 
     def moments(self, f: torch.Tensor) -> Tuple[torch.Tensor, ...]:
         outs = [self.empty_field() for _ in range(4)]

@@ -422,6 +422,27 @@ int cdbm_step_keep_stage(cdbm_handle* h, const void* f_in, void* f1_out, void* f
     return e == hipSuccess ? CDBM_OK : hip_fail(e, "stage launch");
 }
 
+int cdbm_steps_keep_stages(cdbm_handle* h, void* const* f, void* const* f1, int nsteps,
+                           void* stream) {
+    if (!h || !f || !f1 || nsteps < 1) return fail(CDBM_EINVAL, "null argument or nsteps < 1");
+    if (!f[nsteps - 1] || !f1[nsteps - 1]) return fail(CDBM_EINVAL, "null buffer");
+    for (int j = 0; j + 1 < nsteps; ++j) {
+        const int rc = cdbm_step_keep_stage(h, f[j], f1[j], f[j + 1], stream);
+        if (rc != CDBM_OK) return rc;
+    }
+    if (comp(h)) return fail(CDBM_EINVAL, "cdbm_steps_keep_stages does not take CDBM_MIXED_COMP");
+    const char* a = (const char*)f[nsteps - 1];
+    const char* b = (const char*)f1[nsteps - 1];
+    if (a < b + h->fbytes && b < a + h->fbytes)
+        return fail(CDBM_EINVAL, "a state and its first stage must not overlap");
+    const int rc = check_device(h);
+    if (rc != CDBM_OK) return rc;
+    hipStream_t st = (hipStream_t)stream;
+    hipError_t e = mixed(h) ? launch_stage<float>(a, nullptr, f1[nsteps - 1], false, h->k, h->sdev, st)
+                            : launch_stage<double>(a, nullptr, f1[nsteps - 1], false, h->k, h->sdev, st);
+    return e == hipSuccess ? CDBM_OK : hip_fail(e, "stage launch");
+}
+
 int cdbm_moments(cdbm_handle* h, const void* f, double* rho, double* ux, double* uy, double* T,
                  void* stream) {
     if (!h || !f || !rho || !ux || !uy || !T) return fail(CDBM_EINVAL, "null argument");

@@ -99,6 +99,18 @@ int cdbm_step_adjoint_stage(cdbm_handle* h, const void* f_n, const void* f1,
     return step_adjoint_entry(h, f_n, f1, lam_np1, lam_n, dL_dtau, stream);
 }
 
+int cdbm_steps_adjoint_stages(cdbm_handle* h, void* const* f, void* const* f1, int nsteps,
+                              void* const* lam, void* stream) {
+    if (!h || !f || !f1 || !lam || nsteps < 1)
+        return fail(CDBM_EINVAL, "null argument or nsteps < 1");
+    for (int j = nsteps - 1, k = 0; j >= 0; --j, k ^= 1) {
+        const int rc =
+            cdbm_step_adjoint_stage(h, f[j], f1[j], lam[k], lam[1 - k], nullptr, stream);
+        if (rc != CDBM_OK) return rc;
+    }
+    return CDBM_OK;
+}
+
 int cdbm_tau_collect(cdbm_handle* h, double* dL_dtau, void* stream) {
     if (!h || !dL_dtau) return fail(CDBM_EINVAL, "null argument");
     if (comp(h)) return fail(CDBM_EINVAL, "the adjoint entry points do not take CDBM_MIXED_COMP");

@@ -10,8 +10,8 @@ initial-equilibrium adjoint maps dL/df0 to the initial fields.  Forward
 states are checkpointed every `every` steps; the backward pass recomputes
 the states of one segment at a time from its checkpoint, and, while a
 segment's first Runge-Kutta stages fit in KEEP_STAGE_BYTES, keeps them
-(cdbm_step_keep_stage) so that the step adjoints need not recompute them
-(cdbm_step_adjoint_stage; the gradients are the same bit for bit).  With
+(cdbm_steps_keep_stages) so that the step adjoints need not recompute them
+(cdbm_steps_adjoint_stages; the gradients are the same bit for bit).  With
 kept stages, two buffer sets let the next segment's recompute run on a
 second stream while the current segment's step adjoints run (the two kinds
 of launch are short on small grids and leave the GPU idle on their own).
@@ -67,6 +67,12 @@ class CDBMRollout(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g_rho, g_ux, g_uy, g_T):
         s: Solver = ctx.solver
+        segs = list(zip(reversed(_segments(ctx.nsteps, ctx.every)), reversed(ctx.ckpts)))
+        nmax = min(ctx.every, ctx.nsteps)
+        fbytes = ctx.f_final.numel() * ctx.f_final.element_size()
+        kept = nmax * fbytes <= KEEP_STAGE_BYTES
+        # the first recompute needs nothing of the incoming gradients
+        rec = _Recompute(s, segs, nmax) if kept else None
         grads = []
         for g in (g_rho, g_ux, g_uy, g_T):
             grads.append(torch.zeros((s.ny, s.nx), dtype=torch.float64, device="cuda")
@@ -76,11 +82,8 @@ class CDBMRollout(torch.autograd.Function):
         dtau = torch.zeros(1, dtype=torch.float64, device="cuda")
         # drop any terms an interrupted reverse pass left in the accumulator
         s.tau_collect(torch.zeros(1, dtype=torch.float64, device="cuda"))
-        segs = list(zip(reversed(_segments(ctx.nsteps, ctx.every)), reversed(ctx.ckpts)))
-        nmax = min(ctx.every, ctx.nsteps)
-        fbytes = ctx.f_final.numel() * ctx.f_final.element_size()
-        if nmax * fbytes <= KEEP_STAGE_BYTES:
-            lam = _reverse_kept(s, segs, nmax, lam, lam_next)
+        if kept:
+            lam = rec.transpose(lam, lam_next)
         else:
             states = [s.empty_f() for _ in range(nmax)]
             for (_, n), ck in segs:
@@ -98,45 +101,54 @@ class CDBMRollout(torch.autograd.Function):
         return (*g0, gtau, None, None, None)
 
 
-def _reverse_kept(s: Solver, segs, nmax: int, lam, lam_next):
-    """Step adjoints of every segment (last first) with kept stages; returns
-    dL/df0.  A segment's states and first stages are recomputed on a side
-    stream into one of two buffer sets while the current stream transposes
-    the segment before it; events order each set's reuse.  The kernels and
-    their inputs are those of a one-stream pass, so the results are too."""
-    main = torch.cuda.current_stream()
-    side = torch.cuda.Stream()
-    side.wait_stream(main)   # checkpoints and buffers were written on main
-    sets = [([s.empty_f() for _ in range(nmax)], [s.empty_f() for _ in range(nmax)],
-             s.empty_f()) for _ in range(2)]
-    ready = [torch.cuda.Event(), torch.cuda.Event()]
-    free = [None, None]
+class _Recompute:
+    """Step adjoints of every segment (last first) with kept stages.  A
+    segment's states and first stages are recomputed on a side stream into one
+    of two buffer sets while the current stream transposes the segment before
+    it; events order each set's reuse.  The kernels and their inputs are those
+    of a one-stream pass, so the results are too."""
 
-    def recompute(k):
-        (_, n), ck = segs[k]
-        states, stages, spare = sets[k % 2]
-        with torch.cuda.stream(side):
-            if free[k % 2] is not None:
-                side.wait_event(free[k % 2])
-            states[0].copy_(ck)
-            for j in range(n):
-                s.step_keep_stage(states[j], stages[j], states[j + 1] if j + 1 < n else spare)
-            ready[k % 2].record(side)
+    def __init__(self, s: Solver, segs, nmax: int):
+        self.s, self.segs = s, segs
+        self.main = torch.cuda.current_stream()
+        self.side = torch.cuda.Stream()
+        self.side.wait_stream(self.main)   # checkpoints and buffers belong to main
+        self.sets = []
+        for _ in range(2):   # one allocation per set
+            buf = torch.empty((2 * nmax - 1, s.planes, s.ny, s.nx), dtype=s.dtype, device="cuda")
+            buf.record_stream(self.side)
+            views = buf.unbind(0)
+            self.sets.append((list(views[:nmax - 1]), list(views[nmax - 1:])))
+        self.ready = [torch.cuda.Event(), torch.cuda.Event()]
+        self.free = [None, None]
+        self.recompute(0)
 
-    recompute(0)
-    for k in range(len(segs)):
-        if k + 1 < len(segs):
-            recompute(k + 1)
-        (_, n), _ = segs[k]
-        states, stages, _ = sets[k % 2]
-        main.wait_event(ready[k % 2])
-        for j in reversed(range(n)):
-            s.step_adjoint(states[j], lam, lam_next, f1=stages[j], defer_tau=True)
-            lam, lam_next = lam_next, lam
-        done = torch.cuda.Event()
-        done.record(main)
-        free[k % 2] = done
-    return lam
+    def segment(self, k):
+        (_, n), ck = self.segs[k]
+        states, stages = self.sets[k % 2]
+        return [ck] + states[:n - 1], stages[:n]
+
+    def recompute(self, k):
+        with torch.cuda.stream(self.side):
+            if self.free[k % 2] is not None:
+                self.side.wait_event(self.free[k % 2])
+            self.segs[k][1].record_stream(self.side)
+            self.s.steps_keep_stages(*self.segment(k))
+            self.ready[k % 2].record(self.side)
+
+    def transpose(self, lam, lam_next):
+        """dL/df0 from the adjoint vector of the final state."""
+        for k in range(len(self.segs)):
+            self.main.wait_event(self.ready[k % 2])
+            lam, lam_next = self.s.steps_adjoint_stages(*self.segment(k), lam, lam_next)
+            done = torch.cuda.Event()
+            done.record(self.main)
+            self.free[k % 2] = done
+            # after the launches of segment k, which the host is quicker to queue
+            # than the GPU to run; its buffer set was last read by segment k - 1
+            if k + 1 < len(self.segs):
+                self.recompute(k + 1)
+        return lam
 
 
 def rollout(solver: Solver, rho0, ux0, uy0, T0, tau, nsteps: int, every: int = 100):
