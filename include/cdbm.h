@@ -98,16 +98,17 @@ enum { CDBM_STEP_AUTO = 0, CDBM_STEP_FUSED = 1, CDBM_STEP_SPLIT = 2, CDBM_STEP_F
  *               (EINVAL).
  *   step_form   how cdbm_step runs a time step; all forms give the same
  *               result up to rounding order.  CDBM_STEP_FUSED: both stages
- *               in one launch that streams strips of the grid through LDS
- *               (f crosses HBM once in and once out per step).
+ *               in one launch that streams strips of the grid through the
+ *               chip (f crosses HBM once in and once out per step).
  *               CDBM_STEP_SPLIT: two single-stage launches, one cell per
- *               thread, f^(1) through a handle-owned buffer (faster on small
+ *               lane, f^(1) through a handle-owned buffer (faster on small
  *               grids, where the fused launch has too few strips to fill the
- *               chip).  CDBM_STEP_AUTO: FP64 and mixed grids of one row run
- *               several steps per launch, and grids of up to 256 tiles of
- *               8 x 8 cells one step per launch (both with four lanes per
- *               cell and both stages in LDS); above that split up to 2^19
- *               cells (724 x 724) in the mixed form and 2^18 (512 x 512) in
+ *               chip).  CDBM_STEP_AUTO, for FP64 and mixed grids: several
+ *               steps per launch for grids of one row, one step per launch on
+ *               tiles for grids of up to one 8 x 8 tile per compute unit (128
+ *               x 128) or of more than 2^15 cells and up to one 16 x 16 tile
+ *               per compute unit (about 181^2 to 256^2), both stages in LDS;
+ *               else split up to 600000 cells in the mixed form and 350000 in
  *               FP64, fused
  *               above.  CDBM_STEP_FUSED2 (CDBM_MIXED only): two time steps
  *               per launch (temporal blocking: f crosses HBM once in and

@@ -28,6 +28,7 @@ SOURCES = [
     "kernels_step.hip",
     "kernels_stage.hip",
     "kernels_quad.hip",
+    "kernels_tile.hip",
     "kernels_march.hip",
     "kernels_adjoint.hip",
     "kernels_batch.hip",
@@ -44,6 +45,7 @@ FLAGS = [
 # arguments in registers instead of waiting for a load from a cold cache
 EXTRA = {
     "kernels_march.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
+    "kernels_tile.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
     "kernels_quad.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
     "kernels_stage.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
 }

@@ -201,10 +201,17 @@ constexpr int64_t SPLIT_STEP_CELLS_FP64 = 350000;
 // 253 / 200.
 constexpr int64_t MARCH_STEP_CELLS = 700000;
 
+// One step in one launch on tiles; f1: the first stage, or nullptr.
+hipError_t tile_step(const cdbm_handle* h, const void* fin, void* f1, void* fout, hipStream_t st) {
+    if (h->tile == 16)
+        return mixed(h) ? launch_cell_tile_step<float>(fin, f1, fout, h->k, h->kdev, st)
+                        : launch_cell_tile_step<double>(fin, f1, fout, h->k, h->kdev, st);
+    return mixed(h) ? launch_tile_step<float>(fin, f1, fout, h->k, h->qdev, st)
+                    : launch_tile_step<double>(fin, f1, fout, h->k, h->qdev, st);
+}
+
 hipError_t step_once(const cdbm_handle* h, const void* fin, void* fout, hipStream_t st) {
-    if (h->tile)
-        return mixed(h) ? launch_tile_step<float>(fin, nullptr, fout, h->k, h->qdev, st)
-                        : launch_tile_step<double>(fin, nullptr, fout, h->k, h->qdev, st);
+    if (h->tile) return tile_step(h, fin, nullptr, fout, st);
     if (comp(h)) {
         hipError_t e = launch_stage_comp(fin, nullptr, h->stage, false, h->k, h->sdev, st);
         if (e != hipSuccess) return e;
@@ -283,7 +290,7 @@ int cdbm_create(const cdbm_params* p, cdbm_handle** out) {
     h->two = p->step_form == CDBM_STEP_FUSED2;
     if (p->step_form == CDBM_STEP_AUTO && !comp(h)) {
         h->line = line_steps_per_launch(h->k);
-        h->tile = h->line == 0 && tile_step_fits(h->k);
+        if (h->line == 0) h->tile = tile_step_fits(h->k) ? 8 : cell_tile_fits(h->k) ? 16 : 0;
         if (h->line > 0 || h->tile) h->split = false;
     }
     struct {
@@ -410,8 +417,7 @@ int cdbm_step_keep_stage(cdbm_handle* h, const void* f_in, void* f1_out, void* f
     if (rc != CDBM_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     if (h->tile) {
-        hipError_t e = mixed(h) ? launch_tile_step<float>(f_in, f1_out, f_out, h->k, h->qdev, st)
-                                : launch_tile_step<double>(f_in, f1_out, f_out, h->k, h->qdev, st);
+        hipError_t e = tile_step(h, f_in, f1_out, f_out, st);
         return e == hipSuccess ? CDBM_OK : hip_fail(e, "step launch");
     }
     hipError_t e = mixed(h) ? launch_stage<float>(f_in, nullptr, f1_out, false, h->k, h->sdev, st)

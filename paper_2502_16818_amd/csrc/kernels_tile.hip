@@ -1,0 +1,159 @@
+// Steps of grids of about 181 x 181 to 256 x 256 cells: both Runge-Kutta stages
+// in one launch on tiles of 16 x 16 cells, one cell per lane.
+#include <hip/hip_runtime.h>
+
+#include "launch.hpp"
+#include "row_block.hpp"
+#include "step_fused.hpp"
+
+namespace cdbm {
+
+namespace {
+
+// wrap_or_clamp for an index less than `reach` off the grid: without the
+// division unless the grid is smaller than that.
+__device__ __forceinline__ int tile_index(int i, int n, bool clamp, int reach) {
+    if (n < reach) return wrap_or_clamp(i, n, clamp ? CDBM_ZERO_GRADIENT : CDBM_PERIODIC);
+    if (!clamp) return i < 0 ? i + n : (i >= n ? i - n : i);
+    return min(max(i, 0), n - 1);
+}
+
+// Reads of a tile around one cell, N cells per velocity.
+template <typename S, int N>
+struct TileLd {
+    const S* tile;
+    int here, left[2], right[2], below[2], above[2];   // cells at distance 1, 2
+    __device__ __forceinline__ S operator()(int i, int ox, int oy) const {
+        const int c = ox < 0 ? left[-ox - 1] : ox > 0 ? right[ox - 1]
+                    : oy < 0 ? below[-oy - 1] : oy > 0 ? above[oy - 1] : here;
+        return tile[i * N + c];
+    }
+};
+
+constexpr int CT = 16;                            // tile
+constexpr int CW0 = CT + 8, CN0 = CW0 * CW0;      // f^n around it
+constexpr int CW1 = CT + 4, CN1 = CW1 * CW1;      // f^(1)
+constexpr int CELLS1 = CT * CT + 8 * CT;          // the tile and 2-cell strips at its sides
+constexpr int CT_THREADS = 512;
+static_assert(CELLS1 <= CT_THREADS && CN0 - CT_THREADS == 64, "two passes of the loads");
+
+// One step.  A block takes a 16 x 16 tile: f^n of the 24 x 24 cells around it
+// goes to LDS, stage 1 runs on the tile and the 2-cell strips beside its four
+// sides (384 cells, six waves), stage 2 on the tile's 256 cells.  Bound by
+// latencies (one block per compute unit, two waves per SIMD): the loads of f^n,
+// then two stages of about 500 instructions each.  A step against the two
+// single-stage launches: 256^2 mixed 8.6 -> 7.6 us, FP64 11.8 -> 10.2; 200^2
+// mixed 8.4 -> 7.8, FP64 14.8 -> 10.1.
+template <typename S>
+__global__ void __launch_bounds__(CT_THREADS, 2) k_cell_tile_step(const S* __restrict__ fin,
+                                                                  const KParams* __restrict__ Kd,
+                                                                  int nx, int ny, int bc,
+                                                                  S* __restrict__ fout,
+                                                                  S* __restrict__ f1out) {
+    __shared__ S F0[NV * CN0];
+    __shared__ S F1[NV * CN1];
+    const int64_t cells = (int64_t)nx * ny;
+    const uint32_t per_row = (uint32_t)(nx + CT - 1) / CT;
+    const uint32_t b = band_index(blockIdx.x, gridDim.x), ty = b / per_row;
+    const int x0 = (int)(b - ty * per_row) * CT, y0 = (int)ty * CT;
+    const int tid = threadIdx.x;
+    const bool zx = bc & 1, zy = bc & 2;
+    {
+        // a thread takes one cell, and two velocities of one of the last 64
+        const int e = CT_THREADS + (tid & 63);
+        const int i0 = 2 * __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int gx = tile_index(x0 - 4 + tid % CW0, nx, zx, CW0);
+        const int gy = tile_index(y0 - 4 + tid / CW0, ny, zy, CW0);
+        const int ex = tile_index(x0 - 4 + e % CW0, nx, zx, CW0);
+        const int ey = tile_index(y0 - 4 + e / CW0, ny, zy, CW0);
+        const uint32_t at = (uint32_t)(gy * nx + gx) * (uint32_t)sizeof(S);
+        const uint32_t ae = (uint32_t)(ey * nx + ex) * (uint32_t)sizeof(S);
+        S v[NV], w[2];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) v[i] = *(const S*)((const char*)(fin + i * cells) + at);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) w[i] = *(const S*)((const char*)(fin + (i0 + i) * cells) + ae);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) F0[i * CN0 + tid] = v[i];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) F0[(i0 + i) * CN0 + e] = w[i];
+    }
+    // the lane's cell: the tile row by row, then the strips left, right, above, below
+    const int t = tid;
+    int lx, ly;   // in the cells of F0
+    if (t < CT * CT) {
+        lx = 4 + t % CT;
+        ly = 4 + t / CT;
+    } else {
+        const int u = t - CT * CT, side = u / (2 * CT), v = u % (2 * CT);
+        lx = side < 2 ? (side == 0 ? 2 : CT + 4) + v % 2 : 4 + v % CT;
+        ly = side < 2 ? 4 + v / 2 : (side == 2 ? 2 : CT + 4) + v / CT;
+    }
+    const KParams& K = *Kd;
+    S fc[NV], f1[NV];
+    __syncthreads();
+    if (t < CELLS1) {
+        const int c = ly * CW0 + lx;
+        const TileLd<S, CN0> ld{F0, c, {c - 1, c - 2}, {c + 1, c + 2}, {c - CW0, c - 2 * CW0},
+                                {c + CW0, c + 2 * CW0}};
+        stage_cell_k<S, false>(ld, K, f1);
+        const int c1 = (ly - 2) * CW1 + lx - 2;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            fc[i] = F0[i * CN0 + c];
+            F1[i * CN1 + c1] = f1[i];
+        }
+    }
+    __syncthreads();
+    if (t >= CT * CT) return;
+    const int x = x0 + lx - 4, y = y0 + ly - 4;
+    const bool inside = x < nx && y < ny;
+    const uint32_t at = (uint32_t)(y * nx + x) * (uint32_t)sizeof(S);
+    if (f1out != nullptr && inside) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) *(S*)((char*)(f1out + i * cells) + at) = f1[i];
+    }
+    // f^(1) at a ghost of a zero-gradient side is the edge cell's
+    const int xlo = zx ? max(-2, -x0) : -2, xhi = zx ? min(CT + 1, nx - 1 - x0) : CT + 1;
+    const int ylo = zy ? max(-2, -y0) : -2, yhi = zy ? min(CT + 1, ny - 1 - y0) : CT + 1;
+    auto cell1 = [&](int ox, int oy) {
+        const int cx = min(max(lx - 4 + ox, xlo), xhi), cy = min(max(ly - 4 + oy, ylo), yhi);
+        return (cy + 2) * CW1 + cx + 2;
+    };
+    const TileLd<S, CN1> ld{F1, cell1(0, 0), {cell1(-1, 0), cell1(-2, 0)}, {cell1(1, 0), cell1(2, 0)},
+                            {cell1(0, -1), cell1(0, -2)}, {cell1(0, 1), cell1(0, 2)}};
+    S out[NV];
+    stage_cell_k<S, true>(ld, K, out);
+    if (inside) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+            *(S*)((char*)(fout + i * cells) + at) = fma(S(0.5), fc[i], out[i]);
+    }
+}
+
+}  // namespace
+
+// One block per compute unit at most, as a block's time is its latency; and not
+// below 2^15 cells, where the two single-stage launches have less to do (us,
+// mixed / FP64, tiles against single stages: 144^2 7.5 / 9.8 against 7.2 / 8.8,
+// 160^2 7.6 / 10.1 against 7.3 / 9.0, 200^2 7.8 / 10.1 against 8.4 / 14.8).
+bool cell_tile_fits(const KParams& K) {
+    const int64_t tiles = (int64_t)((K.nx + CT - 1) / CT) * ((K.ny + CT - 1) / CT);
+    return (int64_t)K.nx * K.ny > 1 << 15 && tiles <= device_cus();
+}
+
+template <typename S>
+hipError_t launch_cell_tile_step(const void* fin, void* f1out, void* fout, const KParams& K,
+                                 const KParams* Kd, hipStream_t st) {
+    const dim3 grid(((K.nx + CT - 1) / CT) * ((K.ny + CT - 1) / CT));
+    hipLaunchKernelGGL(k_cell_tile_step<S>, grid, dim3(CT_THREADS), 0, st, (const S*)fin, Kd, K.nx,
+                       K.ny, K.bcx | K.bcy << 1, (S*)fout, (S*)f1out);
+    return hipGetLastError();
+}
+
+template hipError_t launch_cell_tile_step<float>(const void*, void*, void*, const KParams&,
+                                                 const KParams*, hipStream_t);
+template hipError_t launch_cell_tile_step<double>(const void*, void*, void*, const KParams&,
+                                                  const KParams*, hipStream_t);
+
+}  // namespace cdbm

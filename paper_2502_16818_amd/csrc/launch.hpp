@@ -63,6 +63,11 @@ int line_steps_per_launch(const KParams& K);
 template <typename S>
 hipError_t launch_tile_step(const void* fin, void* f1out, void* fout, const KParams& K,
                             const QuadParams* Qd, hipStream_t st);
+// The same on tiles of 16 x 16 cells, one cell per lane (kernels_tile.hip).
+bool cell_tile_fits(const KParams& K);
+template <typename S>
+hipError_t launch_cell_tile_step(const void* fin, void* f1out, void* fout, const KParams& K,
+                                 const KParams* Kd, hipStream_t st);
 template <typename S>
 hipError_t launch_line_steps(const void* fin, void* fout, int steps, const KParams& K,
                              const QuadParams* Qd, hipStream_t st);
