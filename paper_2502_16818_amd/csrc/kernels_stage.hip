@@ -83,6 +83,26 @@ __device__ __forceinline__ void stage_conserved(const Parity& g, StageTable K, d
     q[3] = e2;
 }
 
+// Adds the (rho, j_x, j_y, 2E) of a group's four values to q.
+__device__ __forceinline__ void group_conserved(const double v[4], int group, StageTable K,
+                                                double q[4]) {
+    double sum, x, y;
+    if (group % 2 == 0) {
+        sum = (v[0] + v[2]) + (v[1] + v[3]);
+        x = v[0] - v[2];
+        y = v[1] - v[3];
+    } else {
+        const double s01 = v[0] + v[1], s23 = v[2] + v[3];
+        sum = s01 + s23;
+        x = (v[0] - v[1]) - (v[2] - v[3]);
+        y = s01 - s23;
+    }
+    q[0] += sum;
+    q[1] = fma(K->jv[group], x, q[1]);
+    q[2] = fma(K->jv[group], y, q[2]);
+    q[3] = fma(K->en[group], sum, q[3]);
+}
+
 // One stage with the per-cell arithmetic of the fused step:
 //   STAGE2 == false:  out = f + dt L(f)
 //   STAGE2 == true:   out = base / 2 + (f + dt L(f)) / 2
@@ -107,7 +127,10 @@ __device__ __forceinline__ void stage_conserved(const Parity& g, StageTable K, d
 // and each form the moments.  The y stencils are requested together with the
 // cell's own values (of one wave: those of half of its velocities, the rest and
 // the Heun terms right after the moment arithmetic), so that they arrive during
-// that arithmetic.  Bound by latencies up to about 384 x 384, above by the return
+// that arithmetic; in the compensated form three velocities ahead instead, the
+// residual summed group by group and f and r converted twice, which takes the
+// kernel from 183 to 127 registers and four waves a SIMD (512^2 27.5 -> 26.5 us
+// a step).  Bound by latencies up to about 384 x 384, above by the return
 // path of the vector loads (8 cycles of a CU for a 32-bit load of a wave, 16 for
 // a 64-bit one) and by the FP64 arithmetic.  With x offsets loaded too, blocks of
 // four rows and blocks in the grid's own order, a step of two stages took:
@@ -120,10 +143,11 @@ __device__ __forceinline__ void stage_conserved(const Parity& g, StageTable K, d
 template <typename S, bool COMP, int PARTS>
 struct StageRow {
     S x[PARTS][NVX / PARTS][68];
-    double half[PARTS > 1 ? 1 + COMP : 1][PARTS][PARTS > 1 ? 8 : 1][64];
+    double half[PARTS][PARTS > 1 ? 8 : 1][64];
+    double lost[PARTS][PARTS > 1 && COMP ? 4 : 1][64];
 };
 
-template <int PART, int PARTS, typename Row>
+template <int PART, typename Row>
 __device__ __forceinline__ void exchange_half(Row& half, const double v[8], Parity& g) {
     const int lane = threadIdx.x & 63;
     double c[8];
@@ -143,6 +167,10 @@ __device__ __forceinline__ void stage_part(const S* __restrict__ fin, const S* _
                                            int bc, int x0, int y, StageRow<S, COMP, PARTS>& sh) {
     using A = typename std::conditional<COMP, double, S>::type;
     constexpr int NI = NV / PARTS, I0 = PART * NI, NX = NVX / PARTS, K0 = PART * NX;
+    // velocities whose y stencils are requested with the centres and, by the end
+    // of the moments, with the Heun terms; those beyond that many ahead
+    constexpr int FIRST = PARTS > 1 ? NI : COMP ? 3 : NI / 2;
+    constexpr int AHEAD = COMP && PARTS == 1 ? FIRST : NI;
     const int lane = threadIdx.x & 63, x = x0 + lane;
     const bool px = !(bc & 1), py = !(bc & 2);
     StageLd<S> ld;
@@ -163,7 +191,7 @@ __device__ __forceinline__ void stage_part(const S* __restrict__ fin, const S* _
     }
     const S halo = halo_value<S>(fin, K0, NX, x0, y, nx, ny, px, false);
 #pragma unroll
-    for (int i = 0; i < NI / (3 - PARTS); ++i) load_stencil_y(ld, I0 + i, st[i]);
+    for (int i = 0; i < FIRST; ++i) load_stencil_y(ld, I0 + i, st[i]);
     __builtin_amdgcn_sched_barrier(0);
 
     S (&row)[NX][68] = sh.x[PART];
@@ -177,7 +205,7 @@ __device__ __forceinline__ void stage_part(const S* __restrict__ fin, const S* _
         for (int i = 0; i < NI; ++i) fd[i] = (double)f[i];
         Parity g;
         if constexpr (PARTS == 1) to_parity(fd, g);
-        else exchange_half<PART, PARTS>(sh.half[0], fd, g);
+        else exchange_half<PART>(sh.half, fd, g);
         double q[4];
         stage_conserved(g, K, q);
         Macro m;
@@ -194,6 +222,14 @@ __device__ __forceinline__ void stage_part(const S* __restrict__ fin, const S* _
         }
         nonequilibrium<PARTS == 1 ? 0 : PART, PARTS == 1 ? 2 : PART + 1>(g, m, *K, K->a, neq);
     }
+    if constexpr (COMP) {
+        // converted again below: kept in double over the moments, they and r
+        // would take 40 registers
+#pragma unroll
+        for (int i = 0; i < NI; ++i) materialize(f[i]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) materialize(rf[k]);
+    }
     if (lane < 4 * NX) row[lane >> 2][halo_place()] = halo;
     __builtin_amdgcn_sched_barrier(0);
     // the row is read by the wave that wrote it, whose LDS operations are in order
@@ -201,18 +237,22 @@ __device__ __forceinline__ void stage_part(const S* __restrict__ fin, const S* _
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 #pragma unroll
-    for (int i = NI / (3 - PARTS); i < NI; ++i) load_stencil_y(ld, I0 + i, st[i]);
+    for (int i = FIRST; i < AHEAD; ++i) load_stencil_y(ld, I0 + i, st[i]);
     if constexpr (STAGE2) {
 #pragma unroll
-        for (int i = 0; i < NI; ++i) hb[i] = lb(I0 + i, 0);
+        for (int i = 0; i < AHEAD; ++i) hb[i] = lb(I0 + i, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
 
     const bool inside = x < nx;
     char* const o = (char*)fout + (int64_t)y * pitch + (int64_t)x * (int64_t)sizeof(S);
-    double lost[NI];
+    double lost[4], dm[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
+        if (j + AHEAD < NI) {
+            load_stencil_y(ld, I0 + j + AHEAD, st[j + AHEAD]);
+            if (STAGE2) hb[j + AHEAD] = lb(I0 + j + AHEAD, 0);
+        }
         const int i = I0 + j;
         A cx, cy, nz;
         if constexpr (sizeof(A) == 4) {
@@ -233,7 +273,8 @@ __device__ __forceinline__ void stage_part(const S* __restrict__ fin, const S* _
             if (STAGE2) yv += 0.5 * fi + 0.5 * (double)hb[j];
             else yv += fi;
             v = (S)fma(nz, neq[j], yv);
-            lost[j] = yv - (double)v;
+            lost[j % 4] = yv - (double)v;
+            if (j % 4 == 3) group_conserved(lost, i / 4, K, dm);
         } else {
             const A d = fma(nz, (A)neq[j], adv);
             v = STAGE2 ? fma(A(0.5), fi, d) : fi + d;
@@ -242,14 +283,16 @@ __device__ __forceinline__ void stage_part(const S* __restrict__ fin, const S* _
         if (inside) *(S*)(o + i * ld.plane) = v;
     }
     if constexpr (COMP) {
-        Parity gl;
-        if constexpr (PARTS == 1) to_parity(lost, gl);
-        else exchange_half<PART, PARTS>(sh.half[1], lost, gl);
-        double dm[4];
-        stage_conserved(gl, K, dm);
+        if constexpr (PARTS > 1) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sh.lost[PART][k][lane] = dm[k];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 4; ++k) dm[k] = sh.lost[0][k][lane] + sh.lost[1][k][lane];
+        }
 #pragma unroll
         for (int k = 4 / PARTS * PART; k < 4 / PARTS * (PART + 1); ++k) {
-            double rk = r[k];
+            double rk = (double)rf[k];
             if (STAGE2) rk = 0.5 * (double)lb(NV + k, 0) + 0.5 * rk;
             if (inside) *(S*)(o + (NV + k) * ld.plane) = (S)(rk + dm[k]);
         }
