@@ -172,7 +172,7 @@ __device__ __forceinline__ EqTranspose eq_transpose(const Macro& m, const Parity
 // load for the columns on either side; what a wave reads once (add, the tau
 // slot) is requested with the centres, and the y offsets of four velocities
 // ahead; the fluxes are formed before the waves meet for the equilibrium
-// transpose.  The blocks are numbered in bands (band_index), so that the rows
+// transpose.  The blocks are numbered in bands (row_band_index), so that the rows
 // y +- 2 are in the block's own L2.  Time of a step's two stages (the four-wave
 // block with both lines loaded / one wave per row, loaded / two waves, loaded /
 // x through LDS and bands / this):
@@ -185,6 +185,7 @@ __device__ __forceinline__ EqTranspose eq_transpose(const Macro& m, const Parity
 // 256^2 mixed 18.8 / 18.5 / 19.8.
 struct AdjointArgs {
     int nx, ny, bc;
+    uint32_t band;
     double w_in, w_add, z, dt_tau2;
 };
 
@@ -372,7 +373,7 @@ __global__ void __launch_bounds__(128) k_stage_adjoint(
     double* __restrict__ tau_part, int acc) {
     __shared__ AdjointRow<S> row;
     const uint32_t per_row = (uint32_t)(p.nx + 63) / 64;
-    const uint32_t b = band_index(blockIdx.x, gridDim.x);
+    const uint32_t b = row_band_index(blockIdx.x, gridDim.x, p.band);
     const int y = (int)(b / per_row), x0 = (int)(b - (uint32_t)y * per_row) * 64;
     const AdjointTable K = (AdjointTable)(uintptr_t)Kd;
     const BlockTable I = (BlockTable)(uintptr_t)Bd;
@@ -496,7 +497,7 @@ hipError_t launch_stage_adjoint(const void* g, const void* a, const void* add, v
                                 double* tau_part, bool tau_add, double w_in, double w_add,
                                 const KParams& K, const StageParams* Kd, const KParams* Bd,
                                 hipStream_t st) {
-    const AdjointArgs p{K.nx, K.ny, K.bcx | K.bcy << 1, w_in, w_add, K.z, K.dt / (K.tau * K.tau)};
+    const AdjointArgs p{K.nx, K.ny, K.bcx | K.bcy << 1, row_band(K.nx, K.ny), w_in, w_add, K.z, K.dt / (K.tau * K.tau)};
     hipLaunchKernelGGL(k_stage_adjoint<S>, dim3(stage_adjoint_blocks(K)), dim3(128), 0, st,
                        (const S*)g, (const double*)a, (const double*)add, (double*)out, Kd, Bd, p,
                        tau_part, tau_add ? 1 : 0);

@@ -304,10 +304,10 @@ __global__ void __launch_bounds__(64 * PARTS) k_stage(const S* __restrict__ fin,
                                                       const S* __restrict__ base,
                                                       S* __restrict__ fout,
                                                       const StageParams* __restrict__ Kd, int nx,
-                                                      int ny, int bc) {
+                                                      int ny, int bc, uint32_t band) {
     __shared__ StageRow<S, COMP, PARTS> row;
     const uint32_t per_row = (uint32_t)(nx + 63) / 64;
-    const uint32_t b = band_index(blockIdx.x, gridDim.x);
+    const uint32_t b = row_band_index(blockIdx.x, gridDim.x, band);
     const int y = (int)(b / per_row), x0 = (int)(b - (uint32_t)y * per_row) * 64;
     const StageTable K = (StageTable)(uintptr_t)Kd;
     if (PARTS == 1 || __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0)
@@ -321,12 +321,13 @@ hipError_t stage_launch_parts(const void* fin, const void* base, void* fout, boo
                               const KParams& K, const StageParams* Kd, hipStream_t st) {
     const dim3 grid((unsigned)((K.nx + 63) / 64) * (unsigned)K.ny), block(64 * PARTS);
     const int bc = K.bcx | K.bcy << 1;
+    const uint32_t band = row_band(K.nx, K.ny);
     if (stage2)
         hipLaunchKernelGGL((k_stage<S, true, COMP, PARTS>), grid, block, 0, st, (const S*)fin,
-                           (const S*)base, (S*)fout, Kd, K.nx, K.ny, bc);
+                           (const S*)base, (S*)fout, Kd, K.nx, K.ny, bc, band);
     else
         hipLaunchKernelGGL((k_stage<S, false, COMP, PARTS>), grid, block, 0, st, (const S*)fin,
-                           (const S*)base, (S*)fout, Kd, K.nx, K.ny, bc);
+                           (const S*)base, (S*)fout, Kd, K.nx, K.ny, bc, band);
     return hipGetLastError();
 }
 

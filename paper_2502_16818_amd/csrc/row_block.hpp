@@ -16,6 +16,23 @@ __device__ __forceinline__ uint32_t band_index(uint32_t b, uint32_t n) {
     return b < 8 * per ? (b % 8) * per + b / 8 : b;
 }
 
+// The same for blocks of 64 cells of a row, in bands of row_band() blocks.  Up to
+// 2^21 cells an XCD's blocks are one band of an eighth of the rows.  Above, where
+// the grid outgrows the caches, eight fronts that far apart in every plane cost
+// more than the shared rows give, and the bands are eight rows that follow each
+// other (one band / bands of eight rows: compensated steps 1024^2 87 / 90 us,
+// 2000^2 404 / 396, 4096^2 1766 / 1611; stage adjoints of an FP64 step 1024^2
+// 286 / 307, 1800^2 836 / 816, 2048^2 1160 / 1076).
+inline uint32_t row_band(int nx, int ny) {   // 0: one band per XCD
+    return (int64_t)nx * ny <= 1 << 21 ? 0 : 8 * ((uint32_t)(nx + 63) / 64);
+}
+__device__ __forceinline__ uint32_t row_band_index(uint32_t b, uint32_t n, uint32_t band) {
+    if (band == 0) return band_index(b, n);
+    const uint32_t first = b / (8 * band) * (8 * band);
+    if (first + 8 * band > n) return b;
+    return first + (b - first) % 8 * band + (b - first) / 8;
+}
+
 // wrap_or_clamp for an index at most 2 off the grid.
 __device__ __forceinline__ int wrap_by_two(int i, int n, bool periodic) {
     if (periodic) {

@@ -47,3 +47,20 @@ def test_compensated_step_follows_fp64(nx, ny, bc_x):
     err = ((got - want).abs().max() / want.abs().max()).item()
     print(f"  max error {err:.2e}")
     assert err < 2 * 7 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("nx,ny", [(1500, 1399), (4000, 525), (40000, 53)])
+def test_large_grids_in_short_bands(nx, ny):
+    """More than 2^21 cells, where the blocks are numbered in bands of eight
+    rows, with rows left over: the split step and the kept-stage step against
+    the fused step."""
+    from paper_2502_16818_amd import Solver
+    from paper_2502_16818_amd.cdbm import STEP_FUSED, STEP_SPLIT
+    run = W.random_periodic(nx, ny, seed=nx + ny, dt=1e-6, tau=1e-5)
+    run.bc_y = W.ZERO_GRADIENT
+    print(f"[case] {nx}x{ny}", flush=True)
+    a, b = (Solver.from_run(run, MIXED, form) for form in (STEP_FUSED, STEP_SPLIT))
+    f = a.init(run.rho, run.ux, run.uy, run.T)
+    want = a.step(f, nsteps=1)
+    assert torch.equal(b.step(f, nsteps=1), want)
+    assert torch.equal(b.step_keep_stage(f)[1], want)
