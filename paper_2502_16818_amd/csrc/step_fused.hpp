@@ -18,7 +18,8 @@
 // step, and stage 1 is recomputed only on the 2-column x halo (60 columns
 // for 56 outputs).  The global loads of iteration t+1 are issued during
 // iteration t, in two halves: before stage 1 and before stage 2.  This strip
-// serves FP64 storage; FP32 storage uses the wider strip of step_wide.hpp.
+// serves FP64 storage in batches and on grids below 700000 cells (larger ones
+// march, step_march.hpp); FP32 storage uses the wider strip of step_wide.hpp.
 //
 // Boundary conditions: f^n ghost cells are loaded through the periodic wrap
 // or the edge clamp, which is exactly the ghost fill of the scheme.  For a

@@ -15,8 +15,8 @@
 // (their element index is q mod 4), and a cell's four values of a group are
 // one 16- or 32-byte read.
 //
-// The operations and their order are those of stage_cell_k (and, in the
-// compensated form, of k_stage_comp), so the results are bitwise the same.
+// The operations and their order are those of stage_cell_k, so the results are
+// bitwise the same.
 // A velocity that moves towards smaller indices is the mirror image of one
 // that moves towards larger ones: with the stencil read backwards, the sign
 // of its difference and that of its coefficient cancel exactly.  A sign per
