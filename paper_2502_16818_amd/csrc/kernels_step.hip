@@ -1,5 +1,6 @@
 // Fused CDBM time step on one grid: one launch per step, each block
-// streaming down strips of the grid (step_fused.hpp, step_wide.hpp).
+// streaming down strips of the grid (step_fused.hpp, step_wide.hpp); FP64 grids
+// of 700000 cells and more march instead (kernels_march.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -129,15 +130,11 @@ struct Launch {
 // spare units, k = ceil(nstrips / spare) tails on the busiest one; L
 // minimises max(L + fill, k (T + fill)) (4096 x 4096 in FP32: 35
 // strips of 120 columns, 7 pieces of 567 rows and 11 units taking 3 or 4 tails of 127 rows, against
-// 7 pieces of 586 rows and 11 idle units; FP64, 74 strips of 56 columns:
-// 3 pieces of 1232 rows and 34 units taking 2 or 3 tails of 400 rows).  The
-// launch takes the cheaper form.  A persistent grid that splits the
+// 7 pieces of 586 rows and 11 idle units).  The launch takes the cheaper form.  A persistent grid that splits the
 // strip-major sequence of (strip, row) evenly over the compute units
 // balances the rows exactly but loses the row alignment of neighbouring
 // strips and their shared halo lines in L2 (18 % slower at 4096 x 4096 in
-// FP32, 1 % in FP64, whose step is bound more by latency: one wave per row,
-// 6 waves per compute unit); it serves grids too short for pieces of 32
-// rows.
+// FP32); it serves grids too short for pieces of 32 rows.
 constexpr int FILL_ROWS = 12;
 // The two-step strip fills a pipeline four stages deep: 16 halo rows.
 constexpr int FILL_ROWS_TWO = 24;
