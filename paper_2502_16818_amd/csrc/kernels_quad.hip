@@ -25,41 +25,49 @@ __device__ __forceinline__ int wrap_near(int i, int n, int bc, int reach) {
     return min(max(i, 0), n - 1);
 }
 
-// One step of a two-dimensional grid.  A block takes an 8 x 8 tile: f^n of
-// the 16 x 16 cells around it goes to LDS, stage 1 runs on the tile and the
-// 2-cell strips beside its four sides (128 cells, one quad each), stage 2 on
-// the tile's 64 cells.  The corners of the halo are not needed: the stencils
-// are crosses.  Bound by latencies: of about 6.2 us from launch to launch at
+// One step of a two-dimensional grid.  A block takes a tile of 8 x TY cells (TY =
+// 8 or 4): f^n of the 16 x (TY + 8) cells around it goes to LDS, stage 1 runs on
+// the tile and the 2-cell strips beside its four sides (128 cells for TY = 8, one
+// quad each), stage 2 on the tile's own.  The corners of the halo are not needed:
+// the stencils are crosses.  Bound by latencies: of about 6.2 us from launch to launch at
 // 100 x 100 in FP64, 1.6 are stage 1 (two waves per SIMD), 0.8 stage 2, the
 // rest until f^n is in LDS and between the launches.  Tiles are numbered in
 // bands (band_index): 100 x 100 FP64 7.6 -> 6.2 us, 128 x 128 mixed 6.5 -> 5.0.
 // One step of 100 x 100 in FP64 14.7 -> 6.2 us against the two launches of one
 // cell per lane; a call of one step on 32 x 32 (mixed) 11.3 -> 8.3 us.
-constexpr int TILE = 8, TW0 = TILE + 8, TN0 = TW0 * TW0, TW1 = TILE + 4, TN1 = TW1 * TW1;
-constexpr int TILE_THREADS = 4 * (TILE * TILE + 8 * TILE);
+constexpr int TILE = 8, TW0 = TILE + 8, TW1 = TILE + 4;   // columns of the tile, F0 and F1
+template <int TY>
+struct TileRows {
+    static constexpr int H0 = TY + 8, N0 = TW0 * H0, H1 = TY + 4, N1 = TW1 * H1;
+    static constexpr int QUADS = TILE * TY + 4 * TY + 4 * TILE;   // stage 1
+    static constexpr int GROUPS = 2;   // of four velocities, that a thread loads of a cell
+    static constexpr int THREADS = N0 * 4 / GROUPS;
+    static_assert(4 * QUADS <= THREADS && QUADS % 16 == 0 && N0 % 64 == 0, "whole waves");
+};
 
-template <typename S>
-__global__ void __launch_bounds__(TILE_THREADS) k_tile_step(const S* __restrict__ fin,
+template <typename S, int TY>
+__global__ void __launch_bounds__(TileRows<TY>::THREADS) k_tile_step(const S* __restrict__ fin,
                                                             const QuadParams* __restrict__ Qd,
                                                             int nx, int ny, int bc,
                                                             S* __restrict__ fout,
                                                             S* __restrict__ f1out) {
+    constexpr int TN0 = TileRows<TY>::N0, TN1 = TileRows<TY>::N1, H0 = TileRows<TY>::H0;
     __shared__ __attribute__((aligned(32))) S F0[NV * TN0];
     __shared__ __attribute__((aligned(32))) S F1[NV * TN1];
     const int64_t cells = (int64_t)nx * ny;
     const uint32_t per_row = (uint32_t)(nx + TILE - 1) / TILE;
     const uint32_t b = band_index(blockIdx.x, gridDim.x), ty = b / per_row;
-    const int x0 = (int)(b - ty * per_row) * TILE, y0 = (int)ty * TILE;
+    const int x0 = (int)(b - ty * per_row) * TILE, y0 = (int)ty * TY;
     const int tid = threadIdx.x, q = tid & 3;
     const QuadLane L = quad_lane(q);
     QuadConst<S> Q;
     {
-        const int cell = tid & (TN0 - 1);
+        const int cell = tid % TN0;
         const int gx = wrap_near(x0 - 4 + (cell & (TW0 - 1)), nx, bc_x(bc), TW0);
-        const int gy = wrap_near(y0 - 4 + cell / TW0, ny, bc_y(bc), TW0);
+        const int gy = wrap_near(y0 - 4 + cell / TW0, ny, bc_y(bc), H0);
         // a thread takes whole groups of its cell, so that each goes to LDS in
         // one piece; the planes' starts are scalar, the offset within one 32 bits
-        constexpr int GRP = TN0 * 4 / TILE_THREADS;
+        constexpr int GRP = TileRows<TY>::GROUPS;
         const int g0 = __builtin_amdgcn_readfirstlane(tid / TN0) * GRP;
         const uint32_t off = (uint32_t)(gy * nx + gx) * (uint32_t)sizeof(S);
         typename Quad4<S>::type v[GRP];
@@ -76,32 +84,36 @@ __global__ void __launch_bounds__(TILE_THREADS) k_tile_step(const S* __restrict_
     // the quad's cell: the tile row by row, then the strips left, right, above, below
     const int t = tid >> 2;
     int lx, ly;   // in the 16 x 16 cells
-    if (t < TILE * TILE) {
+    if (t < TILE * TY) {
         lx = 4 + t % TILE;
         ly = 4 + t / TILE;
+    } else if (t < TILE * TY + 4 * TY) {
+        const int u = t - TILE * TY, v = u % (2 * TY);
+        lx = (u < 2 * TY ? 2 : TILE + 4) + v % 2;
+        ly = 4 + v / 2;
     } else {
-        const int u = t - TILE * TILE, side = u / (2 * TILE), v = u % (2 * TILE);
-        lx = side < 2 ? (side == 0 ? 2 : TILE + 4) + v % 2 : 4 + v % TILE;
-        ly = side < 2 ? 4 + v / 2 : (side == 2 ? 2 : TILE + 4) + v / TILE;
+        const int u = t - TILE * TY - 4 * TY, v = u % (2 * TILE);
+        lx = 4 + v % TILE;
+        ly = (u < 2 * TILE ? 2 : TY + 4) + v / TILE;
     }
     const bool zx = bc_x(bc) == CDBM_ZERO_GRADIENT, zy = bc_y(bc) == CDBM_ZERO_GRADIENT;
     const int xlo = zx ? max(0, 4 - x0) : 0, xhi = zx ? min(TW0 - 1, nx - 1 - x0 + 4) : TW0 - 1;
-    const int ylo = zy ? max(0, 4 - y0) : 0, yhi = zy ? min(TW0 - 1, ny - 1 - y0 + 4) : TW0 - 1;
+    const int ylo = zy ? max(0, 4 - y0) : 0, yhi = zy ? min(H0 - 1, ny - 1 - y0 + 4) : H0 - 1;
     const int here = ly * TW0 + lx;
     const QuadStencil st0 = quad_stencil<false>(L, lx, ly, TW0, xlo, xhi, ylo, yhi);
     __syncthreads();
-    S fc[4], f1[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) fc[g] = F0[(g * TN0 + here) * 4 + q];
-    {
-        quad_stage<S, TN0, false, false>(F0, here, st0, fc, L, Q, f1);
-    }
     const int here1 = (ly - 2) * TW1 + lx - 2;
+    S fc[4], f1[4];
+    if (t < TileRows<TY>::QUADS) {   // whole waves
 #pragma unroll
-    for (int g = 0; g < 4; ++g) F1[(g * TN1 + here1) * 4 + q] = f1[g];
+        for (int g = 0; g < 4; ++g) fc[g] = F0[(g * TN0 + here) * 4 + q];
+        quad_stage<S, TN0, false, false>(F0, here, st0, fc, L, Q, f1);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) F1[(g * TN1 + here1) * 4 + q] = f1[g];
+    }
     __syncthreads();
     const int x = x0 + lx - 4, y = y0 + ly - 4;
-    if (t >= TILE * TILE) return;   // whole waves
+    if (t >= TILE * TY) return;   // whole waves
     const bool inside = x < nx && y < ny;
     // byte offset of the cell in the plane of the lane's velocity, from group a's
     const uint32_t at = ((uint32_t)q * (uint32_t)cells + (uint32_t)(y * nx + x)) * (uint32_t)sizeof(S);
@@ -114,7 +126,7 @@ __global__ void __launch_bounds__(TILE_THREADS) k_tile_step(const S* __restrict_
     {
         const QuadStencil st =
             quad_stencil<false>(L, lx - 2, ly - 2, TW1, max(xlo - 2, 0), min(xhi - 2, TW1 - 1),
-                                max(ylo - 2, 0), min(yhi - 2, TW1 - 1));
+                                max(ylo - 2, 0), min(yhi - 2, TileRows<TY>::H1 - 1));
         quad_stage<S, TN1, true, false>(F1, here1, st, f1, L, Q, out);
     }
     if (inside) {
@@ -219,13 +231,25 @@ int line_steps_per_launch(const KParams& K) {
     return best;
 }
 
+template <typename S, int TY>
+hipError_t launch_tile_rows(const void* fin, void* f1out, void* fout, const KParams& K,
+                            const QuadParams* Qd, hipStream_t st) {
+    const dim3 grid(((K.nx + TILE - 1) / TILE) * ((K.ny + TY - 1) / TY));
+    hipLaunchKernelGGL((k_tile_step<S, TY>), grid, dim3(TileRows<TY>::THREADS), 0, st,
+                       (const S*)fin, Qd, K.nx, K.ny, K.bcx | K.bcy << 1, (S*)fout, (S*)f1out);
+    return hipGetLastError();
+}
+
 template <typename S>
 hipError_t launch_tile_step(const void* fin, void* f1out, void* fout, const KParams& K,
                             const QuadParams* Qd, hipStream_t st) {
-    const dim3 grid(((K.nx + TILE - 1) / TILE) * ((K.ny + TILE - 1) / TILE));
-    hipLaunchKernelGGL(k_tile_step<S>, grid, dim3(TILE_THREADS), 0, st, (const S*)fin, Qd, K.nx,
-                       K.ny, K.bcx | K.bcy << 1, (S*)fout, (S*)f1out);
-    return hipGetLastError();
+    // Tiles of four rows while there is at most one per compute unit: a tile of
+    // eight has two waves per SIMD in stage 1, one of four little more than one
+    // (32 x 32 mixed 4.59 -> 4.45 us, FP64 5.42 -> 4.91; 88 x 88 FP64 5.85 -> 5.38);
+    // a second round costs more (96 x 96 mixed 7.0 against 4.9).
+    if ((int64_t)((K.nx + TILE - 1) / TILE) * ((K.ny + 3) / 4) <= device_cus())
+        return launch_tile_rows<S, 4>(fin, f1out, fout, K, Qd, st);
+    return launch_tile_rows<S, TILE>(fin, f1out, fout, K, Qd, st);
 }
 
 template <typename S>
