@@ -105,9 +105,9 @@ enum { CDBM_STEP_AUTO = 0, CDBM_STEP_FUSED = 1, CDBM_STEP_SPLIT = 2, CDBM_STEP_F
  *               grids, where the fused launch has too few strips to fill the
  *               chip).  CDBM_STEP_AUTO, for FP64 and mixed grids: several
  *               steps per launch for grids of one row, one step per launch on
- *               tiles for grids of up to one 8 x 8 tile per compute unit (128
- *               x 128) or of more than 2^15 cells and up to one 16 x 16 tile
- *               per compute unit (about 181^2 to 256^2), both stages in LDS;
+ *               tiles for grids of up to one 8 x 8, one 16 x 8 or (above 2^15
+ *               cells) one 16 x 16 tile per compute unit (128 x 128, about 181
+ *               x 181, 256 x 256), both stages in LDS;
  *               else split up to 600000 cells in the mixed form and 350000 in
  *               FP64, fused
  *               above.  CDBM_STEP_FUSED2 (CDBM_MIXED only): two time steps

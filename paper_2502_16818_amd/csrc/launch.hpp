@@ -63,7 +63,7 @@ int line_steps_per_launch(const KParams& K);
 template <typename S>
 hipError_t launch_tile_step(const void* fin, void* f1out, void* fout, const KParams& K,
                             const QuadParams* Qd, hipStream_t st);
-// The same on tiles of 16 x 16 cells, one cell per lane (kernels_tile.hip).
+// The same on tiles of 16 x 8 or 16 x 16 cells, one cell per lane (kernels_tile.hip).
 bool cell_tile_fits(const KParams& K);
 template <typename S>
 hipError_t launch_cell_tile_step(const void* fin, void* f1out, void* fout, const KParams& K,

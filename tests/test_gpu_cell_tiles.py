@@ -26,3 +26,10 @@ def test_tiles_equal_single_stages(nx, ny, bc_x, bc_y):
             assert torch.equal(a.step(f, nsteps=steps), b.step(f, nsteps=steps))
         for x, y in zip(a.step_keep_stage(f), b.step_keep_stage(f)):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("bc", [0, 1])
+@pytest.mark.parametrize("nx,ny", [(136, 136), (176, 180), (181, 170), (17, 1020), (2000, 15), (5, 2040)])
+def test_half_tiles_equal_single_stages(nx, ny, bc):
+    """16 x 8 tiles, up to one per compute unit."""
+    test_tiles_equal_single_stages(nx, ny, bc, 1 - bc if nx % 2 else bc)
