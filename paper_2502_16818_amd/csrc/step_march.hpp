@@ -29,6 +29,7 @@
 // two barriers per six rows, its stencils read from LDS) took 263.
 #pragma once
 
+#include "march_order.hpp"
 #include "row_block.hpp"
 #include "step_fused.hpp"
 
@@ -52,8 +53,12 @@ typedef unsigned MarchBits __attribute__((ext_vector_type(2)));
 typedef double MarchPair __attribute__((ext_vector_type(2)));
 
 struct MarchLds {
-    double half[2][2][7][64];        // by stage and part: parity combinations
-    MarchPair heun[2][2][4][64];     // by part and row parity: f^n between the stages
+    // by buffer and part: parity combinations.  march_buffer() gives the buffer of
+    // an exchange; between a wave's reads of one and the other wave's next write
+    // to it lies the barrier of the exchange between them
+    double half[2][2][7][64];
+    // by part and row parity: f^n between the stages; a lane reads what it wrote
+    MarchPair heun[2][2][4][64];
 };
 
 // minmod() of values that are results of arithmetic: fmin and fmax of double
@@ -298,9 +303,10 @@ struct March {
         }
     }
 
-    // Iteration a; STAGES: how many of the two stages run.
+    // Iteration a; STAGES: how many of the two stages run; first: the buffer of
+    // stage 1's exchange.
     template <int STAGES>
-    __device__ __forceinline__ void iterate(int a, int yb) {
+    __device__ __forceinline__ void iterate(int a, int yb, int first) {
         if constexpr (STAGES == 0) {
             march_take(s1, pre);
             load(a + 1);
@@ -312,7 +318,7 @@ struct March {
         MarchPair(*hs)[64] = lds.heun[q][c1 & 1];
         {
             double fc[8];
-            march_stage<false>(s1, pre, K, q, lds.half[0], fc, f1);
+            march_stage<false>(s1, pre, K, q, lds.half[first], fc, f1);
             // the Heun term of row c2 comes out of LDS, that of row c1 goes in
             if constexpr (STAGES == 2) {
 #pragma unroll
@@ -350,7 +356,7 @@ struct March {
             double r[8];
             {
                 double fc[8];
-                march_stage<true>(s2, v2, K, q, lds.half[1], fc, r);
+                march_stage<true>(s2, v2, K, q, lds.half[march_buffer(MARCH_TAKE + MARCH_ONE, 1)], fc, r);
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -401,15 +407,18 @@ __device__ __forceinline__ void march_strip(const double* __restrict__ fin, doub
                                             MarchTable K, int nx, int ny, int bcx, int bcy, int x0,
                                             int ya, int yb, int part, MarchLds& lds) {
     March<EDGE> m(fin, fout, K, nx, ny, bcx, bcy, x0, ya, part, lds);
-    int a = ya - 4;
+    const int a0 = ya - 4;
+    int a = a0;
 #pragma unroll 1
-    for (; a < ya; ++a) m.template iterate<0>(a, yb);
+    for (; a < a0 + MARCH_TAKE; ++a) m.template iterate<0>(a, yb, 0);
 #pragma unroll 1
-    for (; a < ya + 4; ++a) m.template iterate<1>(a, yb);
+    for (; a < a0 + MARCH_TAKE + MARCH_ONE; ++a)
+        m.template iterate<1>(a, yb, march_buffer(a - a0, 0));
+    constexpr int first = march_buffer(MARCH_TAKE + MARCH_ONE, 0);
 #pragma unroll 1
     for (; a < yb + 4; a += 2) {
-        m.template iterate<2>(a, yb);
-        m.template iterate<2>(a + 1, yb);
+        m.template iterate<2>(a, yb, first);
+        m.template iterate<2>(a + 1, yb, first);
     }
 }
 
