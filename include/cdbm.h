@@ -255,9 +255,10 @@ int cdbm_step_keep_stage(cdbm_handle* h, const void* f_in, void* f1_out, void* f
  * f[j] + dt L(f[j]) for every step j, and f[j + 1] is step j's result for
  * j + 1 < nsteps (the last step's result is not formed).  f and f1: host
  * arrays of nsteps device buffers as in cdbm_step_keep_stage, pairwise
- * non-overlapping; only f[0] is read before it is written.  The same values
- * as nsteps calls of cdbm_step_keep_stage bit for bit, and the same freedom to
- * run beside the handle's step adjoints. */
+ * non-overlapping; only f[0] is read before it is written.  All buffers are
+ * checked before anything is queued.  The same values as nsteps calls of
+ * cdbm_step_keep_stage bit for bit, and the same freedom to run beside the
+ * handle's step adjoints. */
 int cdbm_steps_keep_stages(cdbm_handle* h, void* const* f, void* const* f1, int nsteps,
                            void* stream);
 
@@ -273,7 +274,9 @@ int cdbm_step_adjoint_stage(cdbm_handle* h, const void* f_n, const void* f1,
  * nsteps - 1 down to step 0 (f, f1 as cdbm_steps_keep_stages leaves them):
  * the adjoint vector of the state after the last step in lam[0], that of f[0]
  * in lam[nsteps % 2] afterwards; both buffers are overwritten (each once or
- * more when nsteps > 1). */
+ * more when nsteps > 1), and neither may overlap the other, a state or a first
+ * stage that is still to be read.  All buffers are checked before anything is
+ * queued. */
 int cdbm_steps_adjoint_stages(cdbm_handle* h, void* const* f, void* const* f1, int nsteps,
                               void* const* lam, void* stream);
 

@@ -2,9 +2,12 @@
 // checks, buffer ping-pong, graph capture of the step loop.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -50,6 +53,12 @@ int ensure_buffer(cdbm_handle* h, void** buf) {
         *buf = nullptr;
         return fail(CDBM_ENOMEM, "hipMalloc of an f-sized buffer failed");
     }
+    return CDBM_OK;
+}
+
+int check_segment(void* const* f, void* const* f1, int n) {
+    for (int j = 0; j < n; ++j)
+        if (!f[j] || !f1[j]) return fail(CDBM_EINVAL, "null buffer");
     return CDBM_OK;
 }
 
@@ -428,21 +437,36 @@ int cdbm_step_keep_stage(cdbm_handle* h, const void* f_in, void* f1_out, void* f
     return e == hipSuccess ? CDBM_OK : hip_fail(e, "stage launch");
 }
 
+namespace {
+// Are the 2 n buffers f[0 .. n), f1[0 .. n) of `bytes` each pairwise disjoint?
+int check_disjoint(void* const* f, void* const* f1, int n, size_t bytes) {
+    std::unique_ptr<uintptr_t[]> at(new (std::nothrow) uintptr_t[2 * (size_t)n]);
+    if (!at) return fail(CDBM_ENOMEM, "host allocation failed");
+    for (int j = 0; j < n; ++j) {
+        at[2 * j] = (uintptr_t)f[j];
+        at[2 * j + 1] = (uintptr_t)f1[j];
+    }
+    std::sort(at.get(), at.get() + 2 * n);
+    for (int k = 1; k < 2 * n; ++k)
+        if (at[k] - at[k - 1] < bytes)
+            return fail(CDBM_EINVAL, "the states and first stages must not overlap");
+    return CDBM_OK;
+}
+}  // namespace
+
 int cdbm_steps_keep_stages(cdbm_handle* h, void* const* f, void* const* f1, int nsteps,
                            void* stream) {
     if (!h || !f || !f1 || nsteps < 1) return fail(CDBM_EINVAL, "null argument or nsteps < 1");
-    if (!f[nsteps - 1] || !f1[nsteps - 1]) return fail(CDBM_EINVAL, "null buffer");
+    if (comp(h)) return fail(CDBM_EINVAL, "cdbm_steps_keep_stages does not take CDBM_MIXED_COMP");
+    int rc = check_segment(f, f1, nsteps);
+    if (rc == CDBM_OK) rc = check_disjoint(f, f1, nsteps, h->fbytes);
+    if (rc == CDBM_OK) rc = check_device(h);
+    if (rc != CDBM_OK) return rc;
     for (int j = 0; j + 1 < nsteps; ++j) {
-        const int rc = cdbm_step_keep_stage(h, f[j], f1[j], f[j + 1], stream);
+        rc = cdbm_step_keep_stage(h, f[j], f1[j], f[j + 1], stream);
         if (rc != CDBM_OK) return rc;
     }
-    if (comp(h)) return fail(CDBM_EINVAL, "cdbm_steps_keep_stages does not take CDBM_MIXED_COMP");
-    const char* a = (const char*)f[nsteps - 1];
-    const char* b = (const char*)f1[nsteps - 1];
-    if (a < b + h->fbytes && b < a + h->fbytes)
-        return fail(CDBM_EINVAL, "a state and its first stage must not overlap");
-    const int rc = check_device(h);
-    if (rc != CDBM_OK) return rc;
+    const void* a = f[nsteps - 1];
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = mixed(h) ? launch_stage<float>(a, nullptr, f1[nsteps - 1], false, h->k, h->sdev, st)
                             : launch_stage<double>(a, nullptr, f1[nsteps - 1], false, h->k, h->sdev, st);

@@ -53,13 +53,6 @@ int step_adjoint_impl(cdbm_handle* h, const void* f_n, const void* f1, const voi
     return CDBM_OK;
 }
 
-// Do [a, a + an) and [b, b + bn) intersect?
-bool overlaps(const void* a, size_t an, const void* b, size_t bn) {
-    const char* x = (const char*)a;
-    const char* y = (const char*)b;
-    return x < y + bn && y < x + an;
-}
-
 // Checks and buffers shared by both step adjoints (f1 may be nullptr).
 int step_adjoint_entry(cdbm_handle* h, const void* f_n, const void* f1, const void* lam_np1,
                        void* lam_n, double* dL_dtau, void* stream) {
@@ -103,9 +96,21 @@ int cdbm_steps_adjoint_stages(cdbm_handle* h, void* const* f, void* const* f1, i
                               void* const* lam, void* stream) {
     if (!h || !f || !f1 || !lam || nsteps < 1)
         return fail(CDBM_EINVAL, "null argument or nsteps < 1");
+    if (comp(h)) return fail(CDBM_EINVAL, "the adjoint entry points do not take CDBM_MIXED_COMP");
+    int rc = check_segment(f, f1, nsteps);
+    if (rc != CDBM_OK) return rc;
+    if (!lam[0] || !lam[1]) return fail(CDBM_EINVAL, "null buffer");
+    // lam[1] is first written by the last step, lam[0] by the one before it:
+    // neither may overlap what is read from then on
+    const size_t lbytes = sizeof(double) * (size_t)NV * (size_t)h->cells;
+    if (overlaps(lam[0], lbytes, lam[1], lbytes))
+        return fail(CDBM_EINVAL, "the buffers of the adjoint vectors overlap");
+    for (int k = 0; k < 2; ++k)
+        for (int j = 0; j < nsteps - 1 + k; ++j)
+            if (overlaps(lam[k], lbytes, f[j], h->fbytes) || overlaps(lam[k], lbytes, f1[j], h->fbytes))
+                return fail(CDBM_EINVAL, "an adjoint vector overlaps a state or a first stage");
     for (int j = nsteps - 1, k = 0; j >= 0; --j, k ^= 1) {
-        const int rc =
-            cdbm_step_adjoint_stage(h, f[j], f1[j], lam[k], lam[1 - k], nullptr, stream);
+        rc = cdbm_step_adjoint_stage(h, f[j], f1[j], lam[k], lam[1 - k], nullptr, stream);
         if (rc != CDBM_OK) return rc;
     }
     return CDBM_OK;

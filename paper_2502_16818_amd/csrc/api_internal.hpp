@@ -79,6 +79,14 @@ inline bool comp(const cdbm_handle* h) { return h->p.precision == CDBM_MIXED_COM
 inline int state_planes(int precision) { return precision == CDBM_MIXED_COMP ? NV + 4 : NV; }
 int check_device(const cdbm_handle* h);
 int ensure_buffer(cdbm_handle* h, void** buf);
+// Do [a, a + an) and [b, b + bn) intersect?
+inline bool overlaps(const void* a, size_t an, const void* b, size_t bn) {
+    const char* x = (const char*)a;
+    const char* y = (const char*)b;
+    return x < y + bn && y < x + an;
+}
+// The buffers of a segment of n steps: CDBM_OK if none of f, f1 is null.
+int check_segment(void* const* f, void* const* f1, int n);
 int check_fields_range(int* flag, const double* rho, const double* ux, const double* uy,
                        const double* T, int64_t cells, hipStream_t st);
 

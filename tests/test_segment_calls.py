@@ -47,3 +47,49 @@ def test_segment_equals_single_calls(nx, ny, n, precision):
     assert torch.equal(s.tau_collect(), want_tau)
     with pytest.raises(Exception, match="overlap"):
         s.steps_keep_stages([f0], [f0])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ny", [(40, 24), (200, 150)])
+def test_a_refused_segment_writes_nothing(nx, ny):
+    """A null or overlapping buffer anywhere in the lists, not only beside its step."""
+    import ctypes
+
+    from paper_2502_16818_amd import Solver, cdbm
+    run = W.random_periodic(nx, ny, seed=5, dt=1e-4, tau=2e-4)
+    s = Solver.from_run(run, MIXED)
+    f0 = s.init(run.rho, run.ux, run.uy, run.T)
+    n, one = 3, f0.numel()
+    pool = torch.full((2 * n - 1, *f0.shape), float("nan"), dtype=f0.dtype, device="cuda")
+    f, f1 = [f0, *pool[:n - 1]], list(pool[n - 1:])
+    s.steps_keep_stages(f, f1)
+    lam = [torch.ones((16, ny, nx), dtype=torch.float64, device="cuda") for _ in range(2)]
+    s.steps_adjoint_stages(f, f1, *lam)   # accepted as they are
+    s.tau_collect()
+    pool.fill_(float("nan"))
+    half = pool.view(-1)[one // 2:one // 2 + one].view_as(f0)   # across the first two of the pool
+
+    def ptrs(ts):
+        return (ctypes.c_void_p * len(ts))(*[None if t is None else t.data_ptr() for t in ts])
+
+    def keep(f, f1):
+        return cdbm.load().cdbm_steps_keep_stages(s._h, ptrs(f), ptrs(f1), n, None)
+
+    for bad_f, bad_1 in [(f, [*f1[:2], None]), ([*f[:2], None], f1), (f, [*f1[:2], f0]),
+                         (f, [*f1[:2], f[1]]), ([*f[:2], f1[0]], f1), (f, [*f1[:2], half])]:
+        assert keep(bad_f, bad_1) == -1
+        assert torch.isnan(pool).all()
+
+    def adjoint(f, f1, lam):
+        return cdbm.load().cdbm_steps_adjoint_stages(s._h, ptrs(f), ptrs(f1), n, ptrs(lam), None)
+
+    for t in lam:
+        t.fill_(1.0)
+    pool.fill_(1.0)
+    want = f0.clone()
+    for bad_f, bad_1, bad_l in [([None, *f[1:]], f1, lam), (f, [None, *f1[1:]], lam), (f, f1, [lam[0], None]),
+                                (f, f1, [lam[0], lam[0]]), (f, f1, [lam[0], f0]), (f, f1, [f0, lam[1]]),
+                                (f, f1, [f1[1], lam[1]])]:
+        assert adjoint(bad_f, bad_1, bad_l) == -1
+        assert (lam[0] == 1).all() and (lam[1] == 1).all() and (pool == 1).all()
+        assert torch.equal(f0, want)
