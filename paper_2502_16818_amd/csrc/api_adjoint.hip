@@ -63,7 +63,9 @@ int step_adjoint_entry(cdbm_handle* h, const void* f_n, const void* f1, const vo
         return fail(CDBM_EINVAL, "lam_n overlaps f1");
     int rc = check_device(h);
     if (rc != CDBM_OK) return rc;
-    if (!f1 && (rc = ensure_buffer(h, &h->stage)) != CDBM_OK) return rc;
+    // The small grids that step without a stage buffer get it with their first
+    // adjoint of either kind, as they get lam_mid: a capture cannot allocate.
+    if ((!f1 || h->tile || h->line > 0) && (rc = ensure_buffer(h, &h->stage)) != CDBM_OK) return rc;
     if (!h->lam_mid &&
         hipMalloc(&h->lam_mid, sizeof(double) * (size_t)NV * (size_t)h->cells) != hipSuccess) {
         h->lam_mid = nullptr;
