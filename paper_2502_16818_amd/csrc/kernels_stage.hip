@@ -307,8 +307,8 @@ __global__ void __launch_bounds__(64 * PARTS) k_stage(const S* __restrict__ fin,
                                                       int ny, int bc, uint32_t band) {
     __shared__ StageRow<S, COMP, PARTS> row;
     const uint32_t per_row = (uint32_t)(nx + 63) / 64;
-    const uint32_t b = row_band_index(blockIdx.x, gridDim.x, band);
-    const int y = (int)(b / per_row), x0 = (int)(b - (uint32_t)y * per_row) * 64;
+    const BlockPlace b = block_place(blockIdx.x, gridDim.x, band, per_row, (uint32_t)ny);
+    const int y = (int)b.y, x0 = (int)b.x * 64;
     const StageTable K = (StageTable)(uintptr_t)Kd;
     if (PARTS == 1 || __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0)
         stage_part<S, STAGE2, COMP, 0, PARTS>(fin, base, fout, K, nx, ny, bc, x0, y, row);
