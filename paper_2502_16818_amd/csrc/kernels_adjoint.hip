@@ -172,7 +172,7 @@ __device__ __forceinline__ EqTranspose eq_transpose(const Macro& m, const Parity
 // load for the columns on either side; what a wave reads once (add, the tau
 // slot) is requested with the centres, and the y offsets of four velocities
 // ahead; the fluxes are formed before the waves meet for the equilibrium
-// transpose.  The blocks are numbered in bands (block_place), so that the rows
+// transpose.  The blocks are numbered in bands (row_band_index), so that the rows
 // y +- 2 are in the block's own L2.  Time of a step's two stages (the four-wave
 // block with both lines loaded / one wave per row, loaded / two waves, loaded /
 // x through LDS and bands / this):
@@ -373,15 +373,14 @@ __global__ void __launch_bounds__(128) k_stage_adjoint(
     double* __restrict__ tau_part, int acc) {
     __shared__ AdjointRow<S> row;
     const uint32_t per_row = (uint32_t)(p.nx + 63) / 64;
-    const BlockPlace b = block_place(blockIdx.x, gridDim.x, p.band, per_row, (uint32_t)p.ny);
-    const int y = (int)b.y, x0 = (int)b.x * 64;
-    double* const tau_slot = tau_part + (b.y * per_row + b.x);   // whatever the numbering
+    const uint32_t b = row_band_index(blockIdx.x, gridDim.x, p.band);
+    const int y = (int)(b / per_row), x0 = (int)(b - (uint32_t)y * per_row) * 64;
     const AdjointTable K = (AdjointTable)(uintptr_t)Kd;
     const BlockTable I = (BlockTable)(uintptr_t)Bd;
     if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0)
-        stage_adjoint_part<S, 0>(g, a, add, out, K, I, p, x0, y, tau_slot, acc, row);
+        stage_adjoint_part<S, 0>(g, a, add, out, K, I, p, x0, y, tau_part + b, acc, row);
     else
-        stage_adjoint_part<S, 1>(g, a, add, out, K, I, p, x0, y, tau_slot, acc, row);
+        stage_adjoint_part<S, 1>(g, a, add, out, K, I, p, x0, y, tau_part + b, acc, row);
 }
 
 // Sum of part[i], part[i + step], ... (i < n) over the 1024 threads of a

@@ -299,16 +299,26 @@ __device__ __forceinline__ void stage_part(const S* __restrict__ fin, const S* _
     }
 }
 
-template <typename S, bool STAGE2, bool COMP, int PARTS>
+// COLUMNS: the blocks' bands are columns (COLUMN_BAND_ROWS), else rows in bands of
+// `band` (row_band).
+template <typename S, bool STAGE2, bool COMP, int PARTS, bool COLUMNS>
 __global__ void __launch_bounds__(64 * PARTS) k_stage(const S* __restrict__ fin,
                                                       const S* __restrict__ base,
                                                       S* __restrict__ fout,
                                                       const StageParams* __restrict__ Kd, int nx,
                                                       int ny, int bc, uint32_t band) {
     __shared__ StageRow<S, COMP, PARTS> row;
-    const uint32_t per_row = (uint32_t)(nx + 63) / 64;
-    const BlockPlace b = block_place(blockIdx.x, gridDim.x, band, per_row, (uint32_t)ny);
-    const int y = (int)b.y, x0 = (int)b.x * 64;
+    int x0, y;
+    if constexpr (COLUMNS) {
+        const uint32_t b = band_index(blockIdx.x, gridDim.x), column = b / (uint32_t)ny;
+        x0 = (int)column * 64;
+        y = (int)(b - column * (uint32_t)ny);
+    } else {
+        const uint32_t per_row = (uint32_t)(nx + 63) / 64;
+        const uint32_t b = row_band_index(blockIdx.x, gridDim.x, band);
+        y = (int)(b / per_row);
+        x0 = (int)(b - (uint32_t)y * per_row) * 64;
+    }
     const StageTable K = (StageTable)(uintptr_t)Kd;
     if (PARTS == 1 || __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0)
         stage_part<S, STAGE2, COMP, 0, PARTS>(fin, base, fout, K, nx, ny, bc, x0, y, row);
@@ -316,17 +326,17 @@ __global__ void __launch_bounds__(64 * PARTS) k_stage(const S* __restrict__ fin,
         stage_part<S, STAGE2, COMP, PARTS - 1, PARTS>(fin, base, fout, K, nx, ny, bc, x0, y, row);
 }
 
-template <typename S, bool COMP, int PARTS>
+template <typename S, bool COMP, int PARTS, bool COLUMNS>
 hipError_t stage_launch_parts(const void* fin, const void* base, void* fout, bool stage2,
                               const KParams& K, const StageParams* Kd, hipStream_t st) {
     const dim3 grid((unsigned)((K.nx + 63) / 64) * (unsigned)K.ny), block(64 * PARTS);
     const int bc = K.bcx | K.bcy << 1;
     const uint32_t band = row_band(K.nx, K.ny);
     if (stage2)
-        hipLaunchKernelGGL((k_stage<S, true, COMP, PARTS>), grid, block, 0, st, (const S*)fin,
+        hipLaunchKernelGGL((k_stage<S, true, COMP, PARTS, COLUMNS>), grid, block, 0, st, (const S*)fin,
                            (const S*)base, (S*)fout, Kd, K.nx, K.ny, bc, band);
     else
-        hipLaunchKernelGGL((k_stage<S, false, COMP, PARTS>), grid, block, 0, st, (const S*)fin,
+        hipLaunchKernelGGL((k_stage<S, false, COMP, PARTS, COLUMNS>), grid, block, 0, st, (const S*)fin,
                            (const S*)base, (S*)fout, Kd, K.nx, K.ny, bc, band);
     return hipGetLastError();
 }
@@ -340,12 +350,22 @@ hipError_t stage_launch_parts(const void* fin, const void* base, void* fout, boo
 //   400^2 mixed 14.2 / 15.3, FP64 23.3 / 24.2, compensated 21.4 / 23.5.
 constexpr int64_t TWO_WAVE_CELLS = 3 << 15;
 
+// Larger grids of up to this many rows: an eighth of them is four at most, the rows
+// y +- 2 of such a band are mostly other XCDs', and the bands are an eighth of the
+// columns each instead (kept-stage step in the mixed form, rows / columns: 65536 x
+// 11 64.3 / 44.8 us, 65536 x 32 180 / 176, 4096 x 32 12.7 / 12.2; 4096 x 48 15.1 /
+// 15.3, 8192 x 128 61.9 / 65.9; with rows 65536 x 8 .. 31 took 3 to 7 % more than
+// with blocks in the grid's own order).
+constexpr int COLUMN_BAND_ROWS = 32;
+
 template <typename S, bool COMP>
 hipError_t stage_launch(const void* fin, const void* base, void* fout, bool stage2,
                         const KParams& K, const StageParams* Kd, hipStream_t st) {
-    return (int64_t)K.nx * K.ny <= TWO_WAVE_CELLS
-               ? stage_launch_parts<S, COMP, 2>(fin, base, fout, stage2, K, Kd, st)
-               : stage_launch_parts<S, COMP, 1>(fin, base, fout, stage2, K, Kd, st);
+    if ((int64_t)K.nx * K.ny <= TWO_WAVE_CELLS)
+        return stage_launch_parts<S, COMP, 2, false>(fin, base, fout, stage2, K, Kd, st);
+    return K.ny <= COLUMN_BAND_ROWS
+               ? stage_launch_parts<S, COMP, 1, true>(fin, base, fout, stage2, K, Kd, st)
+               : stage_launch_parts<S, COMP, 1, false>(fin, base, fout, stage2, K, Kd, st);
 }
 
 }  // namespace

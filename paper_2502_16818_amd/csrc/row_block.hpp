@@ -22,36 +22,15 @@ __device__ __forceinline__ uint32_t band_index(uint32_t b, uint32_t n) {
 // more than the shared rows give, and the bands are eight rows that follow each
 // other (one band / bands of eight rows: compensated steps 1024^2 87 / 90 us,
 // 2000^2 404 / 396, 4096^2 1766 / 1611; stage adjoints of an FP64 step 1024^2
-// 286 / 307, 1800^2 836 / 816, 2048^2 1160 / 1076).  Where an eighth of the rows is
-// four at most, the rows y +- 2 of a band are mostly other XCDs', and a band is an
-// eighth of the columns instead, if that is eight blocks at least (kept-stage step
-// mixed and adjoint of an FP64 step, rows / columns: 65536 x 11 64.3 / 44.8 and 289 /
-// 249 us, 65536 x 32 180 / 176 and 721 / 622, 4096 x 32 12.7 / 12.2 and 58.1 / 53.0;
-// 8192 x 128 61.9 / 65.9 and 399 / 403; 2048 x 31 9.1 / 9.1 and 30.5 / 29.2).
-constexpr uint32_t COLUMN_BANDS = ~0u;
+// 286 / 307, 1800^2 836 / 816, 2048^2 1160 / 1076).
 inline uint32_t row_band(int nx, int ny) {   // 0: one band per XCD
-    if (ny <= 32 && nx >= 4096) return COLUMN_BANDS;
     return (int64_t)nx * ny <= 1 << 21 ? 0 : 8 * ((uint32_t)(nx + 63) / 64);
 }
-// The block's column (of per_row) and row (of ny).
-struct BlockPlace {
-    uint32_t x, y;
-};
-__device__ __forceinline__ BlockPlace block_place(uint32_t b, uint32_t n, uint32_t band,
-                                                  uint32_t per_row, uint32_t ny) {
-    if (band == COLUMN_BANDS) {
-        const uint32_t i = band_index(b, n), x = i / ny;
-        return {x, i - x * ny};
-    }
-    uint32_t i;
-    if (band == 0) {
-        i = band_index(b, n);
-    } else {
-        const uint32_t first = b / (8 * band) * (8 * band);
-        i = first + 8 * band > n ? b : first + (b - first) % 8 * band + (b - first) / 8;
-    }
-    const uint32_t y = i / per_row;
-    return {i - y * per_row, y};
+__device__ __forceinline__ uint32_t row_band_index(uint32_t b, uint32_t n, uint32_t band) {
+    if (band == 0) return band_index(b, n);
+    const uint32_t first = b / (8 * band) * (8 * band);
+    if (first + 8 * band > n) return b;
+    return first + (b - first) % 8 * band + (b - first) / 8;
 }
 
 // wrap_or_clamp for an index at most 2 off the grid.
