@@ -35,16 +35,30 @@ __device__ __forceinline__ double minmod(double X, double Y) {
     return fmax(fmin(X, Y), fmin(fmax(X, Y), 0.0));
 }
 
+// d + x / 2 and d - x / 2.  Half of a value is exact (unless it is subnormal), so that
+// fusing the two operations changes nothing; which instruction order comes of it
+// is the compiler's choice (written as fma, the strips were 1 % slower).
+template <typename R>
+__device__ __forceinline__ R plus_half(R d, R x) {
+#pragma clang fp contract(fast)
+    return d + R(0.5) * x;
+}
+template <typename R>
+__device__ __forceinline__ R minus_half(R d, R x) {
+#pragma clang fp contract(fast)
+    return d - R(0.5) * x;
+}
+
 // D for a positive component (stencil j-2 .. j+1) and a negative one (j-1 .. j+2).
 template <typename R>
 __device__ __forceinline__ R nnd_pos(R m2, R m1, R c0, R p1) {
     const R d0 = c0 - m1;
-    return d0 + R(0.5) * (minmod(p1 - c0, d0) - minmod(d0, m1 - m2));
+    return plus_half(d0, minmod(p1 - c0, d0) - minmod(d0, m1 - m2));
 }
 template <typename R>
 __device__ __forceinline__ R nnd_neg(R m1, R c0, R p1, R p2) {
     const R d1 = p1 - c0;
-    return d1 - R(0.5) * (minmod(p2 - p1, d1) - minmod(d1, c0 - m1));
+    return minus_half(d1, minmod(p2 - p1, d1) - minmod(d1, c0 - m1));
 }
 
 struct Parity {
@@ -75,7 +89,8 @@ struct Macro {
 };
 
 // Macroscopic fields of the conserved moments rho, j, 2E; inv_a = 1 / (D + I).
-// Fused operations are written out, here and in nonequilibrium(), so that
+// Fused operations are written out, here and in all that an FP64 or mixed step
+// runs, and the compiler makes no others of it (the flags of build.py), so that
 // every kernel rounds the same way whatever else it computes.
 __device__ __forceinline__ Macro macro_of(double rho, double jx, double jy, double e2,
                                           double inv_a) {

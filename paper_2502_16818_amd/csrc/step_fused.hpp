@@ -167,8 +167,8 @@ __device__ __forceinline__ void stage_cell_k(const Ld& ld, const KParams& K, S o
             if (SX[i] != 0) {
                 const S dl = f[i] - ld(i, -1, 0), dr = ld(i, 1, 0) - f[i];
                 const S M = minmod(dr, dl);
-                if (SX[i] > 0) adv = fma(cx[gr], dl + S(0.5) * (M - from_left(M)), adv);
-                else adv = fma(-cx[gr], dr - S(0.5) * (from_right(M) - M), adv);
+                if (SX[i] > 0) adv = fma(cx[gr], plus_half(dl, M - from_left(M)), adv);
+                else adv = fma(-cx[gr], minus_half(dr, from_right(M) - M), adv);
             }
         } else if (SX[i] > 0)
             adv = fma(cx[gr], nnd_pos<S>(ld(i, -2, 0), ld(i, -1, 0), f[i], ld(i, 1, 0)), adv);

@@ -241,9 +241,9 @@ __device__ __forceinline__ A quad_advection(const S* F, int gr, int q, const Qua
                                             A ca, A cxd, A cyd) {
     auto at = [&](int cell) { return (A)F[(gr * NC + cell) * 4 + q]; };
     if ((gr & 1) == 0) return ca * nnd_pos<A>(at(st.a[0]), at(st.a[1]), f, at(st.a[2]));
-    A adv = cxd * nnd_pos<A>(at(st.x[0]), at(st.x[1]), f, at(st.x[2]));
-    if constexpr (!LINE) adv += cyd * nnd_pos<A>(at(st.y[0]), at(st.y[1]), f, at(st.y[2]));
-    return adv;
+    const A dx = nnd_pos<A>(at(st.x[0]), at(st.x[1]), f, at(st.x[2]));
+    if constexpr (LINE) return cxd * dx;
+    else return fma(cxd, dx, cyd * nnd_pos<A>(at(st.y[0]), at(st.y[1]), f, at(st.y[2])));
 }
 
 // One stage of the lane's four velocities (groups a .. d) at cell `here`:
