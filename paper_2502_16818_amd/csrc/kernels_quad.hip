@@ -42,7 +42,7 @@ struct TileRows {
     static constexpr int QUADS = TILE * TY + 4 * TY + 4 * TILE;   // stage 1
     static constexpr int GROUPS = 2;   // of four velocities, that a thread loads of a cell
     static constexpr int THREADS = N0 * 4 / GROUPS;
-    static_assert(4 * QUADS <= THREADS && QUADS % 16 == 0 && N0 % 64 == 0, "whole waves");
+    static_assert(GROUPS % 2 == 0 && 4 * QUADS <= THREADS && QUADS % 16 == 0 && N0 % 64 == 0, "whole waves");
 };
 
 template <typename S, int TY>
@@ -78,8 +78,11 @@ __global__ void __launch_bounds__(TileRows<TY>::THREADS) k_tile_step(const S* __
                 v[g][k] = *(const S*)((const char*)(fin + (int64_t)(4 * (g0 + g) + k) * cells) + off);
         Q = quad_const<S>(Qd, L);
 #pragma unroll
-        for (int g = 0; g < GRP; ++g)
+        for (int g = 0; g < GRP; ++g) {   // g0 is even
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[g][k] = quad_negated(g & 1, k) ? -v[g][k] : v[g][k];
             *(typename Quad4<S>::type*)(F0 + ((g0 + g) * TN0 + cell) * 4) = v[g];
+        }
     }
     // the quad's cell: the tile row by row, then the strips left, right, above, below
     const int t = tid >> 2;
@@ -120,7 +123,7 @@ __global__ void __launch_bounds__(TileRows<TY>::THREADS) k_tile_step(const S* __
     if (f1out != nullptr && inside) {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-            *(S*)((char*)(f1out + (int64_t)(4 * g) * cells) + at) = f1[g];
+            *(S*)((char*)(f1out + (int64_t)(4 * g) * cells) + at) = S(quad_sign(L, g)) * f1[g];
     }
     S out[4];
     {
@@ -132,7 +135,8 @@ __global__ void __launch_bounds__(TileRows<TY>::THREADS) k_tile_step(const S* __
     if (inside) {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-            *(S*)((char*)(fout + (int64_t)(4 * g) * cells) + at) = fma(S(0.5), fc[g], out[g]);
+            *(S*)((char*)(fout + (int64_t)(4 * g) * cells) + at) =
+                S(quad_sign(L, g)) * fma(S(0.5), fc[g], out[g]);
     }
 }
 
@@ -165,6 +169,8 @@ __global__ void __launch_bounds__(4 * LINE_CELLS) k_line_steps(const S* __restri
         for (int k = 0; k < 4; ++k)
             v[k] = *(const S*)((const char*)(fin + (int64_t)(4 * g + k) * nx) + off);
         Q = quad_const<S>(Qd, L);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = quad_negated(g & 1, k) ? -v[k] : v[k];
         *(typename Quad4<S>::type*)(F0 + (g * W + cell) * 4) = v;
     }
     const bool zx = bc_x(bc) == CDBM_ZERO_GRADIENT;
@@ -194,7 +200,8 @@ __global__ void __launch_bounds__(4 * LINE_CELLS) k_line_steps(const S* __restri
     if (lx >= 4 * steps && lx < W - 4 * steps && x < nx) {
         const uint32_t at = (uint32_t)(q * nx + x) * (uint32_t)sizeof(S);
 #pragma unroll
-        for (int g = 0; g < 4; ++g) *(S*)((char*)(fout + (int64_t)(4 * g) * nx) + at) = fc[g];
+        for (int g = 0; g < 4; ++g)
+            *(S*)((char*)(fout + (int64_t)(4 * g) * nx) + at) = S(quad_sign(L, g)) * fc[g];
     }
 }
 

@@ -16,12 +16,14 @@
 // one 16- or 32-byte read.
 //
 // The operations and their order are those of stage_cell_k, so the results are
-// bitwise the same.
-// A velocity that moves towards smaller indices is the mirror image of one
-// that moves towards larger ones: with the stencil read backwards, the sign
-// of its difference and that of its coefficient cancel exactly.  A sign per
-// lane (+-1 by fma) selects between the sums and the differences of the
-// unpacking, which is exact as well.
+// bitwise the same, next to infinities and NaN too.
+// A velocity that moves towards smaller indices is treated as the mirror image of
+// one that moves towards larger ones: its values are held with the opposite sign,
+// in LDS and in registers, and its stencil is read backwards, so that its
+// differences are those of the other kernels and its coefficient is that of its
+// mirror image.  (A diagonal velocity is held with the sign of its x component.)
+// A change of sign is exact, and so is a sign per lane (+-1 by fma) that selects
+// between the sums and the differences of the unpacking.
 #pragma once
 
 #include "cell.hpp"
@@ -36,6 +38,29 @@ struct QuadLane {
     bool isx;
     int sa, sx, sy;
 };
+
+// Is velocity k of a group (diagonal: 0 or 1) held with the opposite sign?
+__device__ __forceinline__ constexpr bool quad_negated(int diagonal, int k) {
+    return diagonal ? k == 1 || k == 2 : k >= 2;
+}
+
+// Parity combinations (to_parity) of 16 distributions as they are held.
+__device__ __forceinline__ void quad_parity(const double f[NV], Parity& g) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int a = 8 * q, d = 8 * q + 4;
+        g.ee[3 * q + 0] = f[a + 0] - f[a + 2];
+        g.ee[3 * q + 1] = f[a + 1] - f[a + 3];
+        g.oe[2 * q + 0] = f[a + 0] + f[a + 2];
+        g.eo[2 * q + 0] = f[a + 1] + f[a + 3];
+        const double s01 = f[d + 0] - f[d + 1], s23 = f[d + 3] - f[d + 2];
+        const double d01 = f[d + 0] + f[d + 1], d32 = f[d + 2] + f[d + 3];
+        g.ee[3 * q + 2] = s01 + s23;
+        g.oe[2 * q + 1] = d01 + d32;
+        g.eo[2 * q + 1] = s01 - s23;
+        g.oo[q] = d01 - d32;
+    }
+}
 
 __device__ __forceinline__ QuadLane quad_lane(int q) {
     return QuadLane{q, (q & 1) == 0, q < 2 ? 1 : -1, (q == 0 || q == 3) ? 1 : -1, q < 2 ? 1 : -1};
@@ -126,8 +151,8 @@ __device__ __forceinline__ Macro quad_macro(const Parity& g, const QuadParams::S
 }
 
 // k (f - f^eq) of the lane's four velocities (groups a, b, c, d), k = 2 for
-// the axis groups and 4 for the diagonal ones: nonequilibrium() of the cell,
-// the lane's rows only.
+// the axis groups and 4 for the diagonal ones, as they are held: nonequilibrium()
+// of the cell, the lane's rows only.
 __device__ __forceinline__ void quad_nonequilibrium(const Parity& g, const Macro& m,
                                                     const QuadLane& L,
                                                     const double eep[2][6],
@@ -162,7 +187,7 @@ __device__ __forceinline__ void quad_nonequilibrium(const Parity& g, const Macro
         double s = 0.0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) s = fma(odd[p][c], mo[c], s);
-        out[2 * p] = fma(sa, fma(n2, s, go), te);
+        out[2 * p] = fma(sa, te, fma(n2, s, go));
 
         const int r = 2 * p + 1;
         const double D =
@@ -178,7 +203,7 @@ __device__ __forceinline__ void quad_nonequilibrium(const Parity& g, const Macro
         const double tv = fma(n4, se, g.eo[r]);
         const double tt =
             fma(n4, fma(K.diag[p].ioo[0], moo[0], K.diag[p].ioo[1] * moo[1]), g.oo[p]);
-        out[r] = fma(sx, fma(sy, tt, to), fma(sy, tv, td));
+        out[r] = fma(sx, fma(sy, tv, td), fma(sy, tt, to));
     }
 }
 
@@ -221,7 +246,10 @@ struct Quad4 {
     typedef S type __attribute__((ext_vector_type(4)));
 };
 
-// The 16 distributions of cell `here` of a tile of NC cells.
+// The sign with which the lane's velocity of a group is held.
+__device__ __forceinline__ int quad_sign(const QuadLane& L, int gr) { return gr & 1 ? L.sx : L.sa; }
+
+// The 16 distributions of cell `here` of a tile of NC cells, as they are held.
 template <typename S, int NC>
 __device__ __forceinline__ void quad_cell(const S* F, int here, double fd[NV]) {
     typedef typename Quad4<S>::type V4;
@@ -233,21 +261,31 @@ __device__ __forceinline__ void quad_cell(const S* F, int here, double fd[NV]) {
     }
 }
 
-// Advection term of the lane's velocity of group gr: A is the arithmetic
-// type of the differences, ca / cxd / cyd the coefficients of the velocities
-// towards larger indices.
+// Advection term of the lane's velocity of group gr, as it is held: A is the
+// arithmetic type of the differences, ca / cxd / cyd the coefficients of the
+// velocities towards larger indices.
 template <typename A, typename S, int NC, bool LINE>
-__device__ __forceinline__ A quad_advection(const S* F, int gr, int q, const QuadStencil& st, A f,
-                                            A ca, A cxd, A cyd) {
-    auto at = [&](int cell) { return (A)F[(gr * NC + cell) * 4 + q]; };
+__device__ __forceinline__ A quad_advection(const S* F, int gr, const QuadLane& L,
+                                            const QuadStencil& st, A f, A ca, A cxd, A cyd) {
+    auto at = [&](int cell) { return (A)F[(gr * NC + cell) * 4 + L.q]; };
     if ((gr & 1) == 0) return ca * nnd_pos<A>(at(st.a[0]), at(st.a[1]), f, at(st.a[2]));
     const A dx = nnd_pos<A>(at(st.x[0]), at(st.x[1]), f, at(st.x[2]));
-    if constexpr (LINE) return cxd * dx;
-    else return fma(cxd, dx, cyd * nnd_pos<A>(at(st.y[0]), at(st.y[1]), f, at(st.y[2])));
+    if constexpr (LINE) {
+        return cxd * dx;
+    } else if constexpr (sizeof(A) == 8) {
+        return fma(cxd, dx, cyd * nnd_pos<A>(at(st.y[0]), at(st.y[1]), f, at(st.y[2])));
+    } else {
+        // minmod of a NaN and Y is min(Y, 0) in FP32 (Y in FP64): the differences
+        // along y need the sign of the y component
+        const A s = (A)(L.sx * L.sy), m2 = at(st.y[0]), m1 = at(st.y[1]), p1 = at(st.y[2]);
+        const A d0 = s * (f - m1);
+        const A dy = plus_half(d0, minmod(s * (p1 - f), d0) - minmod(d0, s * (m1 - m2)));
+        return fma(cxd, dx, s * cyd * dy);
+    }
 }
 
 // One stage of the lane's four velocities (groups a .. d) at cell `here`:
-// stage_cell_k of the cell, fc the cell's own values of these velocities.
+// stage_cell_k of the cell, fc the cell's own values of these velocities (all as held).
 template <typename S, int NC, bool HALF, bool LINE>
 __device__ __forceinline__ void quad_stage(const S* F, int here, const QuadStencil& st,
                                            const S fc[4], const QuadLane& L,
@@ -255,7 +293,7 @@ __device__ __forceinline__ void quad_stage(const S* F, int here, const QuadStenc
     double fd[NV];
     quad_cell<S, NC>(F, here, fd);
     Parity g;
-    to_parity(fd, g);
+    quad_parity(fd, g);
     const Macro m = quad_macro(g, C.s);
     double neq[4];
     quad_nonequilibrium(g, m, L, C.eep, C.odd, C.s, neq);
@@ -263,7 +301,7 @@ __device__ __forceinline__ void quad_stage(const S* F, int here, const QuadStenc
 #pragma unroll
     for (int gr = 0; gr < 4; ++gr) {
         const int p = gr >> 1;
-        const S adv = quad_advection<S, S, NC, LINE>(F, gr, L.q, st, fc[gr], h * C.a[p], h * C.x[p], h * C.y[p]);
+        const S adv = quad_advection<S, S, NC, LINE>(F, gr, L, st, fc[gr], h * C.a[p], h * C.x[p], h * C.y[p]);
         const S d = fma(h * C.nz[gr & 1], (S)neq[gr], adv);
         out[gr] = HALF ? fma(S(0.5), fc[gr], d) : fc[gr] + d;
     }
