@@ -216,11 +216,16 @@ bool tile_step_fits(const KParams& K) {
     return (int64_t)((K.nx + TILE - 1) / TILE) * ((K.ny + TILE - 1) / TILE) <= device_cus();
 }
 
-// A launch of k steps costs about 2.4 us and 1.25 us per step and round of
-// one block per compute unit; more steps per launch mean fewer cells written
-// per block, so the best k falls with the length of the row (us per step,
-// FP64, measured for k = 1 / 4 / 7: 500 cells 3.7 / 1.9 / 1.7; 10000 cells
-// 4.0 / 2.9 / 5.4, k = 3 2.4; 65536 cells 10 / 9 / 30).
+// Time of a launch of k steps, in us: about 3 + 1.3 k with at most one block per
+// compute unit, whose waves are bound by their own latency, and 3 + r (k + 0.3) with
+// r of them on the fullest one, which share its SIMDs (FP64; mixed about 0.85 of the
+// part after the 3, which moves no choice).  More steps per launch mean fewer
+// cells written per block.  Measured per step for k = 1 .. 7 (FP64), at 500 cells
+// 4.5 2.8 2.3 2.1 1.9 1.8 1.7, 10000 cells 4.7 2.9 2.4 2.9 2.7 3.5 5.3, 12000 cells
+// 4.7 3.0 3.2 2.9 2.8 3.6 6.2, 20000 cells 5.7 3.8 3.3 3.8 4.6 5.4 9.9, 65536 cells
+// 9.9 8.4 8.4 8.9 11.3 15.7 30.4; mixed 12000 cells 4.1 2.6 2.8 2.6 2.4 3.0 5.3, 65536
+// cells 8.2 6.9 7.1 7.4 9.4 13.0 25.0.  At 16 lengths from 64 to 65536 the choice is the
+// fastest of the seven in both precisions.
 int line_steps_per_launch(const KParams& K) {
     if (K.ny != 1) return 0;
     const int cus = device_cus();
@@ -229,7 +234,7 @@ int line_steps_per_launch(const KParams& K) {
     for (int k = 1; 8 * k < LINE_CELLS; ++k) {
         const int out = LINE_CELLS - 8 * k;
         const int blocks = (K.nx + out - 1) / out, rounds = (blocks + cus - 1) / cus;
-        const double c = (2.0 + rounds * k) / k;
+        const double c = (3.0 + (rounds == 1 ? 1.3 * k : rounds * (k + 0.3))) / k;
         if (k == 1 || c < cost) {
             cost = c;
             best = k;

@@ -51,3 +51,21 @@ def test_step_runs_the_form_of_its_size(nx, ny, precision, kernels):
         want = [k.format(S="double" if p == FP64 else "float", C="true" if p == COMP else "false") for k in kernels]
         assert len(names) == len(want) and all(w in n for w, n in zip(want, names)), names
         assert torch.equal(got, Solver.from_run(run, p, STEP_SPLIT).step(f, nsteps=1))
+
+
+@pytest.mark.parametrize("precision", [FP64, MIXED])
+@pytest.mark.parametrize("nx,per_launch", [(500, 7), (6000, 5), (10000, 3), (12000, 5), (16000, 4), (20000, 3), (65536, 2)])
+def test_steps_per_launch_of_a_row(nx, per_launch, precision):
+    """The number that was fastest when each of 1 to 7 was timed at this length."""
+    from paper_2502_16818_amd import Solver
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the lengths are those of 256 compute units")
+    run = W.random_periodic(nx, 1, seed=nx, dt=1e-6, tau=1e-5)
+    s = Solver.from_run(run, precision)
+    f = s.init(run.rho, run.ux, run.uy, run.T)
+    torch.cuda.synchronize()
+    for steps, launches in ((per_launch, 1), (per_launch + 1, 2)):
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+            s.step(f, nsteps=steps)
+            torch.cuda.synchronize()
+        assert sum("k_line_steps" in e.name for e in prof.events()) == launches
