@@ -56,7 +56,8 @@ struct cdbm_handle {
     void* stage = nullptr;      // f-sized buffer of a stage-1 state (adjoint, split steps)
     bool split = false;         // step as two single-stage launches (small grids)
     bool two = false;           // two steps per launch (CDBM_STEP_FUSED2)
-    int tile = 0;               // one launch per step on tiles of this width (8 or 16), else 0
+    int tile = 0;               // one launch per step: 8 on tiles of 8 x 4 or 8 x 8, 16 on
+                                // tiles of 16 x 8 or 16 x 16 cells; else 0
     int line = 0;               // steps per launch of a one-row grid (0: not that form)
     void* lam_mid = nullptr;    // f-sized buffer for the adjoint's intermediate product
     double* partials = nullptr; // reduction partials

@@ -106,27 +106,25 @@ __device__ __forceinline__ Macro macro_of(double rho, double jx, double jy, doub
     return m;
 }
 
-// `inv_a` = 1 / (D + I).  `z` is a zero offset for the constant-table reads;
-// kernels pass an opaque zero so the compiler reloads the tables where they
-// are used instead of holding them in scalar registers across loops.
-__device__ __forceinline__ Macro macro_from_parity(const Parity& g, const KParams& K, double inv_a,
-                                                   int z = 0) {
+// `inv_a` = 1 / (D + I).
+__device__ __forceinline__ Macro macro_from_parity(const Parity& g, const KParams& K,
+                                                   double inv_a) {
     const double rho = ((g.ee[0] + g.ee[1]) + (g.ee[2] + g.ee[3])) + (g.ee[4] + g.ee[5]);
     double jx = 0.0, jy = 0.0, e2 = 0.0;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        jx = fma(K.jx[c + z], g.oe[c], jx);
-        jy = fma(K.jy[c + z], g.eo[c], jy);
+        jx = fma(K.jx[c], g.oe[c], jx);
+        jy = fma(K.jy[c], g.eo[c], jy);
     }
 #pragma unroll
-    for (int c = 0; c < 6; ++c) e2 = fma(K.en[c + z], g.ee[c], e2);
+    for (int c = 0; c < 6; ++c) e2 = fma(K.en[c], g.ee[c], e2);
     return macro_of(rho, jx, jy, e2, inv_a);
 }
 
 // f^eq of the state m (Eq. (7)), through the raw moments and the shared
 // parity-block inverses; a = D + I.
 __device__ __forceinline__ void equilibrium(const Macro& m, const KParams& K, double a,
-                                            double feq[NV], int z = 0) {
+                                            double feq[NV]) {
     const double ux = m.ux, uy = m.uy, T = m.T;
     const double ux2 = ux * ux, uy2 = uy * uy, u2 = ux2 + uy2, uxy = ux * uy;
     const double aT = a * T;
@@ -140,9 +138,9 @@ __device__ __forceinline__ void equilibrium(const Macro& m, const KParams& K, do
     double hee[6], hoe[4], heo[4], hoo[2];
 #pragma unroll
     for (int r = 0; r < 6; ++r) {
-        double s = K.iee[r][z];
+        double s = K.iee[r][0];
 #pragma unroll
-        for (int c = 1; c < 6; ++c) s = fma(K.iee[r][c + z], mee[c], s);
+        for (int c = 1; c < 6; ++c) s = fma(K.iee[r][c], mee[c], s);
         hee[r] = m.rho * s;
     }
 #pragma unroll
@@ -150,15 +148,15 @@ __device__ __forceinline__ void equilibrium(const Macro& m, const KParams& K, do
         double so = 0.0, se = 0.0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            so = fma(K.ioe[r][c + z], moe[c], so);
-            se = fma(K.ieo[r][c + z], meo[c], se);
+            so = fma(K.ioe[r][c], moe[c], so);
+            se = fma(K.ieo[r][c], meo[c], se);
         }
         hoe[r] = m.rho * so;
         heo[r] = m.rho * se;
     }
 #pragma unroll
     for (int r = 0; r < 2; ++r)
-        hoo[r] = m.rho * fma(K.ioo[r][z], moo[0], K.ioo[r][1 + z] * moo[1]);
+        hoo[r] = m.rho * fma(K.ioo[r][0], moo[0], K.ioo[r][1] * moo[1]);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const int a = 8 * q, d = 8 * q + 4;
@@ -183,7 +181,7 @@ __device__ __forceinline__ void equilibrium(const Macro& m, const KParams& K, do
 // Table: const KParams or const StageParams (in any address space).
 template <int Q0 = 0, int Q1 = 2, class Table>
 __device__ __forceinline__ void nonequilibrium(const Parity& g, const Macro& m, Table& K,
-                                               double a, double* out, int z = 0) {
+                                               double a, double* out) {
     const double ux = m.ux, uy = m.uy, T = m.T;
     const double ux2 = ux * ux, uy2 = uy * uy, u2 = fma(ux, ux, uy2), uxy = ux * uy;
     const double E = fma(a, T, u2);        // u^2 + (D+I) T
@@ -207,22 +205,22 @@ __device__ __forceinline__ void nonequilibrium(const Parity& g, const Macro& m, 
     for (int q = Q0; q < Q1; ++q) {
         const int r0 = 3 * q;   // pair (r0, r0 + 1), axis groups: n2
         const double P =
-            fma(K.eep[q][3 + z], s45, fma(K.eep[q][2 + z], s23, K.eep[q][1 + z] * mee[1]));
-        const double Q = fma(K.eep[q][5 + z], d45, K.eep[q][4 + z] * d23);
-        tee[r0] = fma(n2, P + Q, fma(n2, K.eep[q][z], g.ee[r0]));
-        tee[r0 + 1] = fma(n2, P - Q, fma(n2, K.eep[q][z], g.ee[r0 + 1]));
+            fma(K.eep[q][3], s45, fma(K.eep[q][2], s23, K.eep[q][1] * mee[1]));
+        const double Q = fma(K.eep[q][5], d45, K.eep[q][4] * d23);
+        tee[r0] = fma(n2, P + Q, fma(n2, K.eep[q][0], g.ee[r0]));
+        tee[r0 + 1] = fma(n2, P - Q, fma(n2, K.eep[q][0], g.ee[r0 + 1]));
         const int rd = 3 * q + 2;   // diagonal groups: n4
         const double D =
-            fma(K.ees[q][3 + z], s45, fma(K.ees[q][2 + z], s23, K.ees[q][1 + z] * mee[1]));
-        tee[rd] = fma(n4, D, fma(n4, K.ees[q][z], g.ee[rd]));
+            fma(K.ees[q][3], s45, fma(K.ees[q][2], s23, K.ees[q][1] * mee[1]));
+        tee[rd] = fma(n4, D, fma(n4, K.ees[q][0], g.ee[rd]));
     }
 #pragma unroll
     for (int r = 2 * Q0; r < 2 * Q1; ++r) {
         double so = 0.0, se = 0.0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            so = fma(K.ioe[r][c + z], moe[c], so);
-            se = fma(K.ioe[r][(c < 2 ? c : 5 - c) + z], meo[c], se);   // ieo
+            so = fma(K.ioe[r][c], moe[c], so);
+            se = fma(K.ioe[r][c < 2 ? c : 5 - c], meo[c], se);   // ieo
         }
         const double n = (r & 1) ? n4 : n2;
         toe[r] = fma(n, so, g.oe[r]);
@@ -230,7 +228,7 @@ __device__ __forceinline__ void nonequilibrium(const Parity& g, const Macro& m, 
     }
 #pragma unroll
     for (int r = Q0; r < Q1; ++r)
-        too[r] = fma(n4, fma(K.ioo[r][z], moo[0], K.ioo[r][1 + z] * moo[1]), g.oo[r]);
+        too[r] = fma(n4, fma(K.ioo[r][0], moo[0], K.ioo[r][1] * moo[1]), g.oo[r]);
 #pragma unroll
     for (int q = Q0; q < Q1; ++q) {
         const int a0 = 8 * (q - Q0), d0 = a0 + 4;
@@ -262,6 +260,14 @@ __device__ __forceinline__ int wrap_or_clamp(int i, int n, int bc) {
         return i < 0 ? i + n : i;
     }
     return i < 0 ? 0 : (i >= n ? n - 1 : i);
+}
+
+// The same for an index less than `reach` off the grid: without the division
+// unless the grid is smaller than that.
+__device__ __forceinline__ int wrap_near(int i, int n, int bc, int reach) {
+    if (n < reach) return wrap_or_clamp(i, n, bc);
+    if (bc == CDBM_PERIODIC) return i < 0 ? i + n : (i >= n ? i - n : i);
+    return min(max(i, 0), n - 1);
 }
 
 }  // namespace cdbm

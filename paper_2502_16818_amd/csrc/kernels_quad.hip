@@ -17,14 +17,6 @@ __device__ __forceinline__ int bc_x(int bc) { return bc & 1; }
 __device__ __forceinline__ int bc_y(int bc) { return bc >> 1; }
 static_assert(CDBM_PERIODIC == 0 && CDBM_ZERO_GRADIENT == 1, "one bit each");
 
-// wrap_or_clamp for an index less than `reach` off the grid: without the
-// division unless the grid is smaller than that.
-__device__ __forceinline__ int wrap_near(int i, int n, int bc, int reach) {
-    if (n < reach) return wrap_or_clamp(i, n, bc);
-    if (bc == CDBM_PERIODIC) return i < 0 ? i + n : (i >= n ? i - n : i);
-    return min(max(i, 0), n - 1);
-}
-
 // One step of a two-dimensional grid.  A block takes a tile of 8 x TY cells (TY =
 // 8 or 4): f^n of the 16 x (TY + 8) cells around it goes to LDS, stage 1 runs on
 // the tile and the 2-cell strips beside its four sides (128 cells for TY = 8, one

@@ -10,14 +10,6 @@ namespace cdbm {
 
 namespace {
 
-// wrap_or_clamp for an index less than `reach` off the grid: without the
-// division unless the grid is smaller than that.
-__device__ __forceinline__ int tile_index(int i, int n, bool clamp, int reach) {
-    if (n < reach) return wrap_or_clamp(i, n, clamp ? CDBM_ZERO_GRADIENT : CDBM_PERIODIC);
-    if (!clamp) return i < 0 ? i + n : (i >= n ? i - n : i);
-    return min(max(i, 0), n - 1);
-}
-
 // Reads of a tile around one cell, N cells per velocity.
 template <typename S, int N>
 struct TileLd {
@@ -62,8 +54,8 @@ __global__ void __launch_bounds__(CellTile<TY>::THREADS, 2) k_cell_tile_step(con
     const int tid = threadIdx.x;
     const bool zx = bc & 1, zy = bc & 2;
     {
-        const int gx = tile_index(x0 - 4 + tid % CW0, nx, zx, CW0);
-        const int gy = tile_index(y0 - 4 + tid / CW0, ny, zy, G::H0);
+        const int gx = wrap_near(x0 - 4 + tid % CW0, nx, bc & 1, CW0);
+        const int gy = wrap_near(y0 - 4 + tid / CW0, ny, bc >> 1, G::H0);
         const uint32_t at = (uint32_t)(gy * nx + gx) * (uint32_t)sizeof(S);
         S v[NV], w[2];
 #pragma unroll
@@ -71,8 +63,8 @@ __global__ void __launch_bounds__(CellTile<TY>::THREADS, 2) k_cell_tile_step(con
         const int e = G::THREADS + (tid & 63);
         const int i0 = 2 * __builtin_amdgcn_readfirstlane(tid >> 6);
         if constexpr (G::EXTRA > 0) {
-            const int ex = tile_index(x0 - 4 + e % CW0, nx, zx, CW0);
-            const int ey = tile_index(y0 - 4 + e / CW0, ny, zy, G::H0);
+            const int ex = wrap_near(x0 - 4 + e % CW0, nx, bc & 1, CW0);
+            const int ey = wrap_near(y0 - 4 + e / CW0, ny, bc >> 1, G::H0);
             const uint32_t ae = (uint32_t)(ey * nx + ex) * (uint32_t)sizeof(S);
 #pragma unroll
             for (int i = 0; i < 2; ++i)

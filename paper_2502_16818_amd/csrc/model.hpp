@@ -88,7 +88,10 @@ struct alignas(64) QuadParams {
     // axis pairs odd along x (ioe) and along y (ieo), the NND coefficients
     // -dt v / dr of the first stage of velocities towards larger indices
     // (groups a, c along x and along y, groups b, d along x and along y) and
-    // the relaxation factors of the first stage (KParams::nzq).
+    // the relaxation factors of the first stage (StageParams::cd[0][8 .. 9]: -z / 2
+    // of the axis groups, -z / 4 of the diagonal ones).  The rows along y (oy, and
+    // ieo below) are those along x with columns 2 and 3 swapped; formed from these
+    // in the kernel, 10000 cells in one row took 2.43 us a step against 2.37.
     struct Lane {
         double eep[2][6], ox[2][4], oy[2][4];
         double ax[2], ay[2], dx[2], dy[2], nz[2];
