@@ -89,3 +89,12 @@ def test_traffic_record_scales_by_the_copy(tmp_path, monkeypatch):
     assert rec["bytes_per_launch"] == rec["read_bytes"] + rec["write_bytes"]
     assert rec["kernel_digest"] == bench.kernel_digest()
     assert rec["dispatches"] == [2, 1]
+
+
+def test_traffic_record_is_of_the_present_kernel():
+    """The bench line reports measured HBM traffic only while the kernel's
+    sources hash to the record's digest: a change of them needs new counters."""
+    with open(bench.TRAFFIC_FILE) as fh:
+        rec = json.load(fh)
+    assert rec["kernel"] == bench.KERNEL_NAME
+    assert rec["kernel_digest"] == bench.kernel_digest()
