@@ -105,12 +105,11 @@ enum { CDBM_STEP_AUTO = 0, CDBM_STEP_FUSED = 1, CDBM_STEP_SPLIT = 2, CDBM_STEP_F
  *               grids, where the fused launch has too few strips to fill the
  *               chip).  CDBM_STEP_AUTO, for FP64 and mixed grids: several
  *               steps per launch for grids of one row, one step per launch on
- *               tiles for grids of up to one 8 x 8, one 16 x 8 or (above 2^15
- *               cells) one 16 x 16 tile per compute unit (128 x 128, about 181
- *               x 181, 256 x 256), both stages in LDS;
- *               else split up to 600000 cells in the mixed form and 350000 in
- *               FP64, fused
- *               above.  CDBM_STEP_FUSED2 (CDBM_MIXED only): two time steps
+ *               tiles, both stages in LDS, for grids of up to one 8 x 8, one
+ *               16 x 8 or (above 2^15 cells) one 16 x 16 tile per compute unit
+ *               (with 256 of them squares up to 128 x 128, up to 176 x 176, and
+ *               from 182 x 182 to 256 x 256), else split up to 600000 cells in
+ *               the mixed form and 350000 in FP64, fused above.  CDBM_STEP_FUSED2 (CDBM_MIXED only): two time steps
  *               per launch (temporal blocking: f crosses HBM once in and
  *               once out per two steps, on 48-column strips that carry four
  *               rings of stages in LDS); an odd last step runs fused.  Same

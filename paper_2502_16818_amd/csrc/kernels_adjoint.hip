@@ -178,7 +178,7 @@ __device__ __forceinline__ EqTranspose eq_transpose(const Macro& m, const Parity
 // x through LDS and bands / this):
 //   256^2 mixed 31.6 / 29.9 / 22.9 / 21.2 / 18.5 us, FP64 35.0 / 33.4 / 27.3 / 23.5 / 21.8,
 //   1000 x 777 mixed 297 / 207 / 200 / 206 / 179, FP64 338 / 254 / 289 / 227 / 204,
-//   1800^2 FP64 1474 / 1194 / 1282 / 912 / 835.
+//   1800^2 FP64 1474 / 1194 / 1282 / 912 / 835, and 816 with bands of eight rows.
 // Two rows per block (four waves) cost up to 16 % more on large grids and gain
 // at most 2 % on small ones; without the bands 256^2 FP64 took 10 % more; y
 // offsets 2 / 4 / 8 velocities ahead: 1000 x 777 FP64 211 / 204 / 206 us,

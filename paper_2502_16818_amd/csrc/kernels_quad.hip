@@ -25,6 +25,8 @@ static_assert(CDBM_PERIODIC == 0 && CDBM_ZERO_GRADIENT == 1, "one bit each");
 // 100 x 100 in FP64, 1.6 are stage 1 (two waves per SIMD), 0.8 stage 2, the
 // rest until f^n is in LDS and between the launches.  Tiles are numbered in
 // bands (band_index): 100 x 100 FP64 7.6 -> 6.2 us, 128 x 128 mixed 6.5 -> 5.0.
+// (The signs of the mirrored velocities, step_quad.hpp: 128 x 128 mixed 5.1 -> 5.2
+// us, FP64 6.25 -> 6.28.)
 // One step of 100 x 100 in FP64 14.7 -> 6.2 us against the two launches of one
 // cell per lane; a call of one step on 32 x 32 (mixed) 11.3 -> 8.3 us.
 constexpr int TILE = 8, TW0 = TILE + 8, TW1 = TILE + 4;   // columns of the tile, F0 and F1
@@ -202,7 +204,7 @@ __global__ void __launch_bounds__(4 * LINE_CELLS) k_line_steps(const S* __restri
 // One block per compute unit at most: a block's stages are bound by the
 // latency of two waves per SIMD, and with a second round of blocks the two
 // launches of the single-stage kernels are faster (mixed / FP64: 128 x 128,
-// 256 blocks, 5.0 / 6.2 us against 6.3 / 7.1; 144 x 144, 324 blocks, 7.9 / 9.9
+// 256 blocks, 5.2 / 6.3 us against 6.3 / 7.1; 144 x 144, 324 blocks, 7.9 / 9.9
 // against 7.3 / 8.8; 160 x 160 7.8 / 9.7 against 7.3 / 9.0).
 bool tile_step_fits(const KParams& K) {
     return (int64_t)((K.nx + TILE - 1) / TILE) * ((K.ny + TILE - 1) / TILE) <= device_cus();

@@ -1,5 +1,6 @@
-// Steps of grids of about 129 x 129 to 256 x 256 cells: both Runge-Kutta stages
-// in one launch on tiles of 16 x 8 or 16 x 16 cells, one cell per lane.
+// Steps of grids of about 129 x 129 to 176 x 176 (tiles of 16 x 8 cells) and 182 x
+// 182 to 256 x 256 cells (16 x 16): both Runge-Kutta stages in one launch, one cell
+// per lane.
 #include <hip/hip_runtime.h>
 
 #include "launch.hpp"
@@ -144,10 +145,12 @@ bool half_tiles_fit(const KParams& K) { return cell_tiles(K, 8) <= device_cus();
 // One block per compute unit at most, as a block's time is its latency: tiles of
 // eight rows as long as they fit (us a step, mixed / FP64, against the two
 // single-stage launches: 136^2 6.8 / 8.2 against 7.1 / 8.7, 160^2 6.7 / 8.2 against
-// 7.3 / 9.0, 176^2 6.8 / 8.4 against 7.6 / 9.7), then of sixteen (181^2 8.0 / 10.3,
-// 200^2 7.7 / 10.0 against 8.4 / 14.8, 256^2 7.6 / 10.2 against 8.6 / 11.8).  A narrow
-// grid of up to 2^15 cells that only fits in the latter has less to do in two
-// launches (at 144^2 tiles of sixteen rows took 7.5 / 9.8 against 7.2 / 8.8).
+// 7.3 / 9.0, 176^2 6.8 / 8.4 against 7.6 / 9.7), then of sixteen (200^2 7.7 / 10.0
+// against 8.4 / 14.8, 256^2 7.6 / 10.2 against 8.6 / 11.8).  A grid of up to 2^15 cells
+// that only fits in the latter has less to do in two launches, unless it is very
+// narrow (tiles of sixteen rows / split: 144^2 7.5 / 7.2 and 9.8 / 8.8, 17 x 1100 9.6 /
+// 8.9 and 11.8 / 11.5, 181 x 170 7.9 / 7.9 and 10.1 / 9.7; the squares from 177^2 to
+// 181^2, which run split, 7.7 / 8.0 and 10.0 / 10.3; 9 x 3000 7.6 / 13.6 and 9.4 / 19.6).
 bool cell_tile_fits(const KParams& K) {
     return half_tiles_fit(K) || ((int64_t)K.nx * K.ny > 1 << 15 && cell_tiles(K, 16) <= device_cus());
 }
